@@ -30,19 +30,19 @@ hv_status hv_leaf_schedule(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_b
 /* Leaf-kernel choice for tests and measurements, per calling thread:
  * 0 = automatic (calls with at most 128 leaves per compute unit of
  * the current device -- 32768 on MI355X -- use the two-wave kernel, which
- * moves the message schedule to a second wave and shortens each chunk's chain
- * of blocks; others use the one-wave kernel), 1 = always the
- * one-wave kernel, 2 = always the two-wave kernel, 3 = always the two-wave
- * kernel with two producer/consumer pairs per workgroup (the layout it takes
- * above 64 leaves per compute unit).  Monitor scans (hv_monitor.h) take the
+ * moves the message schedule to other waves (and, with SHA-256, gives a chunk
+ * two lanes) and shortens each chunk's chain of blocks; others use the
+ * one-wave kernel), 1 = always the one-wave kernel, 2 = always the two-wave
+ * kernel, 3 = always the two-wave kernel with twice the chunks, 128, per
+ * workgroup (the layout it takes above 64 leaves per compute unit).  Monitor scans (hv_monitor.h) take the
  * one-wave kernel under the automatic choice.  The same choice applies to
  * SHA-384's two leaf kernels.  The digests do not depend on it.
  * Errors: HV_ERR_INVALID_ARG for another value. */
 hv_status hv_set_leaf_kernel(int choice);
 
 /* The leaf kernel a hash call over n_leaves leaves would run on the current
- * device under this thread's choice: *kernel = 1 (one-wave), 2 (two-wave, one
- * producer/consumer pair per workgroup) or 3 (two-wave, two pairs).  Monitor
+ * device under this thread's choice: *kernel = 1 (one-wave), 2 (two-wave, 64
+ * chunks per workgroup) or 3 (two-wave, 128).  Monitor
  * scans take the one-wave kernel under the automatic choice.
  * Errors: HV_ERR_INVALID_ARG for a NULL kernel. */
 hv_status hv_leaf_kernel_for(uint64_t n_leaves, int* kernel);

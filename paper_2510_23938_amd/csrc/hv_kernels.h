@@ -69,11 +69,11 @@ hipError_t launch_sched_range(const MsgDesc* msgs, const Pair* off, uint32_t n, 
 hipError_t launch_monitor_compare(const uint8_t* digests, const uint8_t* ref, uint64_t first, uint64_t k, uint32_t D,
                                   uint64_t* result, hipStream_t s);
 // The two-wave SHA-256 leaf kernel (sha256_split.hip; same contract as
-// launch_sha256_leaves), with one or two producer/consumer pairs per
-// workgroup.  The automatic choice takes it for up to 128 leaves per compute
-// unit of the current device (32768 on a 256-CU device).
+// launch_sha256_leaves), with one or two groups of 64 chunks per workgroup.
+// The automatic choice takes it for up to 128 leaves per compute unit of the
+// current device (32768 on a 256-CU device).
 hipError_t launch_sha256_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
-                               bool two_pairs, hipStream_t s);
+                               bool two_groups, hipStream_t s);
 // The two-wave SHA-384 leaf kernel (sha384_split.hip; same contract as
 // launch_sha384_leaves), one or two pairs per workgroup.
 hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
@@ -83,14 +83,14 @@ hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t 
 hipError_t launch_sha384_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background = false);
 // The leaf kernel a call over n_slots leaves takes under this thread's choice
-// on the current device: 1 one-wave, 2 two-wave with one pair per workgroup,
-// 3 two-wave with two pairs (both hashes use this rule).
+// on the current device: 1 one-wave, 2 two-wave with 64 chunks per workgroup,
+// 3 two-wave with 128 (both hashes use this rule).
 int leaf_kernel_for(uint64_t n_slots, bool background);
 // Compute units of the current device (queried once per device; 0 if the
 // query fails, which makes the automatic choices take the one-wave kernels).
 uint32_t device_cus();
 // Leaf-kernel choice of the calling thread (hv_set_leaf_kernel): 0 automatic,
-// 1 one-wave kernel, 2 two-wave kernel, 3 two-wave kernel with two pairs per
+// 1 one-wave kernel, 2 two-wave kernel, 3 two-wave kernel with 128 chunks per
 // workgroup.
 int leaf_kernel_choice();
 // SHA-256 leaf digests with the kernel that choice selects (the callers' entry).

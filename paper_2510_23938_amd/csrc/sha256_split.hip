@@ -1,30 +1,59 @@
-// sha256_split.hip -- SHA-256 of every chunk for small leaf counts: two waves
-// per 64 chunks, so that one chunk's chain of blocks runs faster.
+// sha256_split.hip -- SHA-256 of every chunk for small leaf counts: two lanes
+// per chunk and a schedule made by other waves, so that one chunk's chain of
+// blocks runs faster.
 //
-// With fewer chunks than the chip has lanes, the leaf kernel is latency-bound:
-// a chunk is one sequential chain of compressions on one lane, and a lone wave
-// issues about one instruction every four cycles.  Here the message schedule
-// (48 words x 10 operations per block, FIPS 180-4 section 6.2.2 step 1) moves
-// to a second wave: wave 0 builds each block's 64 schedule words -- message
-// words, padding (section 5.1.1) and expansion -- into LDS, and wave 1 runs
-// only the 64 rounds and the feed-forward, reading the words from LDS.  The
-// rounds' dependent path per block shrinks from about 1400 to about 900
-// instructions, while wave 0 prepares the next block on another SIMD.
+// With fewer chunks than the chip has lanes, a chunk's time is the latency of
+// its chain of compressions, and a lone wave issues one VALU instruction every
+// 4.6 to 4.8 cycles whatever its operands: what bounds a block is the number
+// of instructions on the wave that carries the state.  The one-wave kernel has
+// 1405 of them per block.  Two things take instructions off that wave:
 //
-// Synchronisation: the two waves hold the same 64 descriptors and compute the
-// same block count (the wave maximum), and each executes exactly one barrier
-// per block: wave 0 after writing block b's words into buffer b % 2, wave 1
-// before reading them.  Wave 0 refills buffer b % 2 only after the barrier
-// of block b + 1, which wave 1 reaches after its last read of block b.
-// Wave 0 loads each block's bytes one block ahead, so the load latency runs
-// under the previous block's expansion and the barrier wait.
+// 1. Producer waves build each block's 64 schedule words -- message words,
+//    padding (section 5.1.1) and expansion (FIPS 180-4 section 6.2.2 step 1),
+//    each with its round constant added -- into LDS; consumer waves only run
+//    rounds.
+// 2. A chunk has two lanes of a consumer wave.  The a lane holds the last four
+//    values of a (a, b, c, d of the round), the e lane those of e (e, f, g, h):
+//      e' = Sigma1(e) + Ch(e, f, g) + (h + K + W) + d
+//      a' = Sigma0(a) + Maj(a, b, c) + e' - d
+//    Both are sigma(x0) + f(x0, x1, x2) +- x3 + one value of the partner's, so
+//    one instruction stream computes both: the rotations differ by a shift
+//    register, Maj(a, b, c) = Ch(a ^ b, c, b) differs from Ch(e, f, g) =
+//    Ch(~e, g, f) by one masked operation, and -d = (d ^ ~0) + 1 takes the
+//    place of h + K + W (the a lanes read ones as their words).  The a lanes
+//    run two steps behind: then both lanes want the partner's x1, a value one
+//    step old, and the exchange (a DPP operand of the addition) waits for
+//    nothing.  A step is 9 instructions -- 3 alignbit, 3 bitop3, xad, add, add3
+//    -- against 14 for a round on one lane; the two steps of lag and the
+//    selects at a block's ends add 26 to its 576.
+//
+// One 64 KiB chunk takes 1.31 ms (1.28 us per block, 4.8 cycles per
+// instruction) against 1.79 with one lane per chunk and 2.65 with the one-wave
+// kernel, whatever the number of chunks up to 64 per CU; up to 128 per CU 1.70
+// against 1.88 and 2.69.
+//
+// A workgroup holds kGroups groups of 64 chunks, four waves each: two
+// consumers of 32 chunks and two producers, which build alternate blocks and
+// so have two block times for one block (a producer's 64 words are as many
+// instructions as a consumer's block).  Up to 64 chunks per CU, one group per
+// workgroup gives every wave a SIMD of its own.  Up to 128, two groups put one
+// consumer and one producer on each SIMD (waves go to SIMDs in turn): 950
+// instructions per SIMD and block, where two workgroups of one group could
+// place two consumers on one.
+//
+// Synchronisation: every wave of the workgroup computes the same block count
+// (the workgroup's most) and passes barriers 0..blocks.  Block b is produced
+// between barriers b - 1 and b + 1 into buffer b % 3 and read into registers
+// by the consumers after barrier b + 1; a consumer passes barrier b + 2 only
+// when those reads have landed, and buffer b % 3 is next written after barrier
+// b + 2.
 //
 // Exec mask: on gfx950 a wave whose rounds run with most lanes masked off is
 // much slower per instruction than a full one (measured: 16 or fewer active
 // lanes take about 1.6x as long per block as 32 or 64).  So every lane runs
 // every block's expansion and rounds, also dead lanes and lanes past their
-// last block (on zeros or stale words); only the loads, the state update
-// (a select) and the digest store are per lane.
+// last block (on zeros or stale words); only the loads, the state update and
+// the digest store are per lane.
 #include "hv_kernels.h"
 #include "sha256_device.h"
 #include "split_common.h"
@@ -34,11 +63,7 @@
 namespace hv {
 namespace {
 
-// A workgroup holds kPairs producer/consumer pairs (1 or 2): waves 2p build
-// schedules, waves 2p + 1 run rounds.  Up to 64 chunks per CU one pair per
-// workgroup is slightly faster (a two-wave barrier); up to 128 two pairs keep
-// one workgroup, and so one wave per SIMD, on each CU.
-constexpr int kMaxPairs = 2;
+constexpr uint32_t kRow = 65;  // a schedule row: 64 chunks' words, and the ones the a lanes add
 constexpr int kMaxDevices = 64;
 
 // The aligned dwords under block b of a chunk at p with nfull whole blocks and
@@ -101,170 +126,209 @@ __device__ __forceinline__ void whole_block_words(const uint32_t D[17], uint32_t
     for (int i = 0; i < 16; ++i) W[i] = bswap(__builtin_amdgcn_alignbyte(D[i + 1], D[i], sh));
 }
 
-// Wave 0's work for block b: issue the loads of block b + 1 into `nxt`, build
-// block b's 64 schedule words from `cur` into `buf`, then meet wave 1 at the
-// barrier.
+// Producer p's blocks b = p, p + 2, ...: the loads of block b + 2 are issued,
+// then block b's 64 schedule words, each with its round constant, go to buffer
+// b % 3, half before barrier b and half before barrier b + 1.  Two register
+// sets take turns, so that the loads run under the expansion and the barrier
+// waits.  Every producer passes barriers 0..nmax.
 template <bool kAligned>
-__device__ __forceinline__ void produce(uint32_t b, uint64_t src, uint64_t total, uint32_t nfull, uint32_t r,
-                                        uint32_t nblk, uint32_t nfull_min, uint32_t lane, uint4 (*buf)[64],
-                                        const uint32_t cur[17], uint32_t nxt[17]) {
+__device__ __forceinline__ void produce_all(uint32_t p, uint64_t src, uint64_t total, uint32_t nfull, uint32_t r,
+                                            uint32_t nblk, uint32_t nmax, uint32_t nfull_min, uint32_t lane,
+                                            uint4 (*sched)[16][kRow]) {
     const uint32_t sh = kAligned ? 0u : (uint32_t)(src & 3);
-    // `cur` has landed (its loads were issued one block ago); waiting here, on
-    // every path and before the next loads, keeps the compiler from placing a
-    // wait for them where it would also wait for the loads issued below
-    wait_vmem();
-    if (b + 1 < nblk) load_block<kAligned>(src, block_valid(nfull, r, b + 1), b + 1, nxt);
-    {  // every lane, also past its last block: see the kernel's comment on exec
-        uint32_t W[16];
-        if (b < nfull_min)  // wave-uniform: a whole block on every lane
-            whole_block_words(cur, sh, W);
-        else
-            block_words(cur, sh, total, nfull, r, b, W);
+    uint32_t D[2][17];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) buf[g][lane] = make_uint4(W[4 * g], W[4 * g + 1], W[4 * g + 2], W[4 * g + 3]);
+    for (int k = 0; k < 17; ++k) D[0][k] = D[1][k] = 0;
+    if (p < nblk) load_block<kAligned>(src, block_valid(nfull, r, p), p, D[0]);
+    uint32_t passed = 0;  // barriers
+    if (p == 1) {
+        lds_barrier();
+        ++passed;
+    }
+    uint32_t slot = p;  // b % 3
+    for (uint32_t b0 = p; b0 < nmax; b0 += 4) {
 #pragma unroll
-        for (int g = 4; g < 16; ++g) {
-            uint32_t x[4];
+        for (int half = 0; half < 2; ++half) {
+            const uint32_t b = b0 + 2 * half;
+            if (b < nmax) {
+                uint32_t(&cur)[17] = D[half];
+                uint32_t(&nxt)[17] = D[half ^ 1];
+                wait_vmem();  // `cur` has landed; the loads below stay in flight
+                if (b + 2 < nblk) load_block<kAligned>(src, block_valid(nfull, r, b + 2), b + 2, nxt);
+                uint32_t W[16];
+                if (b < nfull_min)
+                    whole_block_words(cur, sh, W);
+                else
+                    block_words(cur, sh, total, nfull, r, b, W);
+                uint4(*buf)[kRow] = sched[slot];
+                slot = slot == 0 ? 2 : slot - 1;  // (b + 2) % 3
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int t = 4 * g + k;
-                const uint32_t w = small_sigma1(W[(t - 2) & 15]) + W[(t - 7) & 15] + small_sigma0(W[(t - 15) & 15]) +
-                                   W[t & 15];
-                W[t & 15] = w;
-                x[k] = w;
+                for (int g = 0; g < 16; ++g) {
+                    uint32_t x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int t = 4 * g + k;
+                        if (t >= 16)
+                            W[t & 15] = small_sigma1(W[(t - 2) & 15]) + W[(t - 7) & 15] +
+                                        small_sigma0(W[(t - 15) & 15]) + W[t & 15];
+                        x[k] = W[t & 15] + kRound[t];
+                    }
+                    buf[g][lane] = make_uint4(x[0], x[1], x[2], x[3]);
+                    if (g == 8) lds_barrier();  // barrier b
+                }
+                lds_barrier();  // barrier b + 1: block b's words are in buf
+                passed += 2;
             }
-            buf[g][lane] = make_uint4(x[0], x[1], x[2], x[3]);
         }
     }
-    lds_barrier();  // block b's words are in buf
+    for (; passed < nmax + 1; ++passed) lds_barrier();
 }
 
-// All of wave 0's blocks.  Two register sets take turns: block b + 1 loads
-// into one while block b is built from the other, so the loads run under the
-// expansion and the barrier wait, and no copy waits on them.
-template <bool kAligned>
-__device__ __forceinline__ void produce_all(uint64_t src, uint64_t total, uint32_t nfull, uint32_t r, uint32_t nblk,
-                                            uint32_t nmax, uint32_t nfull_min, uint32_t lane, uint4 (*sched)[16][64]) {
-    uint32_t A[17], B[17];
+// What tells the two lanes of a chunk apart.
+struct Half {
+    uint32_t r1, r2, r3;  // the lane's three rotations: Sigma0's (a lanes) or Sigma1's (e lanes)
+    uint32_t m;           // ~0 in a lanes, 0 in e lanes
+};
+
+// Step s of the lanes' shared recurrence (see the top of the file): R[(i - s) & 3]
+// is the lane's value i steps old, and the new value takes the oldest one's place.
+__device__ __forceinline__ void step(uint32_t R[4], int s, const Half& c, uint32_t kw) {
+    const uint32_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3], x3 = R[(3 - s) & 3];
+    const uint32_t sigma = xor3(rotr(x0, c.r1), rotr(x0, c.r2), rotr(x0, c.r3));
+    const uint32_t p = __builtin_amdgcn_bitop3_b32(x0, x1, c.m, 0x2D);  // a ^ b, or ~e
+    const uint32_t f = choose(p, x2, x1);                               // Maj(a, b, c), or Ch(e, f, g)
+    uint32_t q;                                                         // -d, or h + K + W: (x3 ^ m) + kw
+    // the compiler would split this into an XOR and share the addition with
+    // the next one, and the lane exchange then needs an instruction of its own
+    asm("v_xad_u32 %0, %1, %2, %3" : "=v"(q) : "v"(x3), "v"(c.m), "v"(kw));
+    q += __builtin_amdgcn_update_dpp(0, x1, 0xB1, 0xf, 0xf, true);  // the partner's x1: quad_perm [1,0,3,2]
+    R[(3 - s) & 3] = sigma + f + q;
+}
+
+// The 64 rounds of one block on its words q (FIPS 180-4 section 6.2.2 steps
+// 2-4): 64 steps of the e lanes, with the a lanes two steps behind.  H holds
+// (H4, H5, H6, H7) in e lanes and (H2, H3, H0, H1) in a lanes, so that the
+// values of step 64 feed forward into H[0] and H[1] in both; the feed-forward
+// only where `on` (the lane still has blocks).
+__device__ __forceinline__ void rounds(uint32_t H[4], const uint4 q[16], const Half& c, bool on) {
+    uint32_t R[4] = {H[0], H[1], H[2], H[3]}, at64[4];
 #pragma unroll
-    for (int k = 0; k < 17; ++k) A[k] = B[k] = 0;
-    if (0 < nblk) load_block<kAligned>(src, block_valid(nfull, r, 0), 0, A);
-    for (uint32_t b = 0; b < nmax; b += 2) {
-        produce<kAligned>(b, src, total, nfull, r, nblk, nfull_min, lane, sched[0], A, B);
-        if (b + 1 < nmax) produce<kAligned>(b + 1, src, total, nfull, r, nblk, nfull_min, lane, sched[1], B, A);
+    for (int s = 0; s < 66; ++s) {
+        const uint4 w = q[(s >> 2) & 15];
+        const uint32_t kw = s >= 64 ? 1u : (s & 3) == 0 ? w.x : (s & 3) == 1 ? w.y : (s & 3) == 2 ? w.z : w.w;
+        if (s == 64)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) at64[i] = R[i];
+        step(R, s, c, kw);
+        // the a lanes' first two values are the block's b and a themselves
+        if (s == 0) R[3] = c.m ? H[3] : R[3];
+        if (s == 1) R[2] = c.m ? H[2] : R[2];
+    }
+    if (on) {
+        H[0] += at64[0];
+        H[1] += at64[1];
+        H[2] += c.m ? R[2] : at64[2];
+        H[3] += c.m ? R[3] : at64[3];
     }
 }
 
-// The 64 rounds of one block on its schedule words q (FIPS 180-4 section
-// 6.2.2 steps 2-4); the feed-forward only where `on` (the lane still has
-// blocks).
-__device__ __forceinline__ void rounds(uint32_t H[8], const uint4 q[16], bool on) {
-    uint32_t s[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = H[i];
-#pragma unroll
-    for (int g = 0; g < 16; ++g) {
-        const uint32_t w4[4] = {q[g].x, q[g].y, q[g].z, q[g].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int t = 4 * g + k;
-            uint32_t& a = s[(8 - t) & 7];
-            uint32_t& bb = s[(9 - t) & 7];
-            uint32_t& c = s[(10 - t) & 7];
-            uint32_t& dd = s[(11 - t) & 7];
-            uint32_t& e = s[(12 - t) & 7];
-            uint32_t& f = s[(13 - t) & 7];
-            uint32_t& gg = s[(14 - t) & 7];
-            uint32_t& h = s[(15 - t) & 7];
-            const uint32_t t1 = h + kRound[t] + w4[k] + big_sigma1(e) + choose(e, f, gg);
-            const uint32_t t2 = big_sigma0(a) + majority(a, bb, c);
-            dd += t1;     // the new e
-            h = t1 + t2;  // the new a
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) H[i] = on ? H[i] + s[i] : H[i];
-}
-
-// The consumer's work for block b: pass the barrier of block b + 1 and issue
-// the reads of its words into `nxt`, then run block b's rounds on `cur`, so
-// the reads land under the rounds.
-__device__ __forceinline__ void consume(uint32_t b, uint32_t nmax, uint32_t nblk, uint32_t lane,
-                                        uint4 (*sched)[16][64], uint32_t H[8], const uint4 cur[16], uint4 nxt[16]) {
+// A consumer's work for block b (its words in `cur`): pass the barrier of
+// block b + 1 and issue the reads of its words into `nxt`, then run block b's
+// rounds, so the reads land under the rounds.  buf: b % 3, moved on.
+__device__ __forceinline__ void consume(uint32_t b, uint32_t& buf, uint32_t nmax, uint32_t nblk, uint32_t col,
+                                        uint4 (*sched)[16][kRow], uint32_t H[4], const Half& c, const uint4 cur[16],
+                                        uint4 nxt[16]) {
     // `cur` has landed (read one block ago); waiting here, on every path and
     // before the next reads, keeps the compiler from placing a wait for it
     // where it would also wait for the reads issued below
     wait_lds();
+    buf = buf == 2 ? 0 : buf + 1;
     if (b + 1 < nmax) {
-        lds_barrier();  // block b + 1's words are in buffer (b + 1) % 2
+        lds_barrier();  // barrier b + 2: block b + 1's words are in its buffer
 #pragma unroll
-        for (int g = 0; g < 16; ++g) nxt[g] = sched[(b + 1) & 1][g][lane];
+        for (int g = 0; g < 16; ++g) nxt[g] = sched[buf][g][col];
     }
-    rounds(H, cur, b < nblk);
+    rounds(H, cur, c, b < nblk);
 }
 
-template <int kPairs>
-__global__ void __launch_bounds__(128 * kPairs) sha256_split_kernel(const LeafDesc* __restrict__ desc,
-                                                                    uint64_t n_slots, uint64_t out_bound,
-                                                                    uint8_t* __restrict__ digests) {
-    // [pair][buffer][group of four words][lane]: lane-consecutive 16-byte entries
-    __shared__ uint4 sched[kPairs][2][16][64];
+template <int kGroups>
+__global__ void __launch_bounds__(256 * kGroups) sha256_chain_kernel(const LeafDesc* __restrict__ desc,
+                                                                     uint64_t n_slots, uint64_t out_bound,
+                                                                     uint8_t* __restrict__ digests) {
+    __shared__ uint4 sched[kGroups][3][16][kRow];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t pair = wave >> 1;
-    const uint64_t base = (uint64_t)blockIdx.x * (64 * kPairs);
-    const uint64_t slot = base + 64 * pair + lane;
-    const bool live = slot < n_slots;
+    const uint32_t group = (wave >> 1) % kGroups;
+    const uint64_t base = ((uint64_t)blockIdx.x * kGroups + group) * 64;
+    // every wave holds its group's 64 descriptors once, for the block counts
+    uint64_t slot = base + lane;
+    bool live = slot < n_slots;
     LeafDesc d = {0, 0, 0};
     if (live) d = desc[slot];
-    const uint32_t nfull = (uint32_t)(d.nbytes >> 6);
-    const uint32_t r = (uint32_t)(d.nbytes & 63);
-    const uint32_t nblk = live ? nfull + (r <= 55 ? 1u : 2u) : 0u;
+    uint32_t nfull = (uint32_t)(d.nbytes >> 6), r = (uint32_t)(d.nbytes & 63);
+    uint32_t nblk = live ? nfull + (r <= 55 ? 1u : 2u) : 0u;
     // every wave of the workgroup runs the same number of barriers: the most
-    // blocks of any of its 128 chunks
-    const uint64_t other = base + 64 * (pair ^ 1) + lane;
-    uint32_t nmax = nblk;
-    if (kPairs == 2 && other < n_slots) {
-        const uint64_t ob = desc[other].nbytes;
-        const uint32_t on = (uint32_t)(ob >> 6) + ((ob & 63) <= 55 ? 1u : 2u);
-        nmax = on > nmax ? on : nmax;
+    // blocks of any of its chunks
+    uint32_t nmax = nblk, nfull_min = live ? nfull : 0xffffffffu;
+    if constexpr (kGroups == 2) {
+        const uint64_t other = ((uint64_t)blockIdx.x * kGroups + (group ^ 1)) * 64 + lane;
+        if (other < n_slots) {
+            const uint64_t ob = desc[other].nbytes;
+            const uint32_t on = (uint32_t)(ob >> 6) + ((ob & 63) <= 55 ? 1u : 2u);
+            nmax = on > nmax ? on : nmax;
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t x = __shfl_xor(nmax, o);
+        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(nfull_min, o);
         nmax = x > nmax ? x : nmax;
+        nfull_min = y < nfull_min ? y : nfull_min;
     }
     nmax = __builtin_amdgcn_readfirstlane(nmax);
+    nfull_min = __builtin_amdgcn_readfirstlane(nfull_min);
 
-    if ((wave & 1) == 0) {
-        // the fewest whole blocks of any live lane of the wave (wave-uniform)
-        uint32_t nfull_min = live ? nfull : 0xffffffffu;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const uint32_t x = __shfl_xor(nfull_min, o);
-            nfull_min = x < nfull_min ? x : nfull_min;
-        }
-        nfull_min = __builtin_amdgcn_readfirstlane(nfull_min);
+    if (wave >= 2 * kGroups) {
+        // the ones of this producer's group (each writes half, before barrier 1)
+        const uint32_t p = wave & 1;
+        if (lane < 24) sched[group][(24 * p + lane) >> 4][(24 * p + lane) & 15][64] = make_uint4(1, 1, 1, 1);
         if (__all((d.src & 15) == 0))
-            produce_all<true>(d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[pair]);
+            produce_all<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[group]);
         else
-            produce_all<false>(d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[pair]);
-    } else {
-        uint32_t H[8];
-        init_state(H);
-        // two register sets take turns: block b + 1's words are read into one
-        // while block b's rounds run on the other
-        uint4 A[16], B[16];
-        if (nmax > 0) {
-            lds_barrier();  // block 0's words are in buffer 0
+            produce_all<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[group]);
+        return;
+    }
+    const uint32_t chunk = 32 * (wave & 1) + (lane >> 1);
+    slot = base + chunk;
+    live = slot < n_slots;
+    if (live) d = desc[slot];
+    nfull = (uint32_t)(d.nbytes >> 6);
+    r = (uint32_t)(d.nbytes & 63);
+    nblk = live ? nfull + (r <= 55 ? 1u : 2u) : 0u;
+    const bool e = lane & 1;
+    const Half c = {e ? 6u : 2u, e ? 11u : 13u, e ? 25u : 22u, e ? 0u : ~0u};
+    uint32_t H[4] = {e ? kInit[4] : kInit[2], e ? kInit[5] : kInit[3], e ? kInit[6] : kInit[0],
+                     e ? kInit[7] : kInit[1]};
+    const uint32_t col = e ? chunk : 64u;
+    // two register sets take turns: block b + 1's words are read into one
+    // while block b's rounds run on the other
+    uint4 A[16], B[16];
+    if (nmax > 0) {
+        lds_barrier();
+        lds_barrier();  // block 0's words are in buffer 0
 #pragma unroll
-            for (int g = 0; g < 16; ++g) A[g] = sched[pair][0][g][lane];
-        }
-        for (uint32_t b = 0; b < nmax; b += 2) {
-            consume(b, nmax, nblk, lane, sched[pair], H, A, B);
-            if (b + 1 < nmax) consume(b + 1, nmax, nblk, lane, sched[pair], H, B, A);
-        }
-        if (live && d.out < out_bound) store_digest(digests + 32 * d.out, H);
+        for (int g = 0; g < 16; ++g) A[g] = sched[group][0][g][col];
+    }
+    uint32_t buf = 0;  // b % 3
+    for (uint32_t b = 0; b < nmax; b += 2) {
+        consume(b, buf, nmax, nblk, col, sched[group], H, c, A, B);
+        if (b + 1 < nmax) consume(b + 1, buf, nmax, nblk, col, sched[group], H, c, B, A);
+    }
+    if (live && d.out < out_bound) {
+        uint4* out = reinterpret_cast<uint4*>(digests + 32 * d.out);
+        if (e)
+            out[1] = make_uint4(bswap(H[0]), bswap(H[1]), bswap(H[2]), bswap(H[3]));
+        else
+            out[0] = make_uint4(bswap(H[2]), bswap(H[3]), bswap(H[0]), bswap(H[1]));
     }
 }
 
@@ -286,12 +350,12 @@ uint32_t device_cus() {
 int leaf_kernel_for(uint64_t n_slots, bool background) {
     const int choice = leaf_kernel_choice();
     const uint64_t cus = device_cus();
-    // the two-wave kernel while every CU holds one workgroup at most (two
-    // pairs: four waves on the CU's four SIMDs); with more, a CU's SIMDs would
-    // each run two waves and the one-wave kernel is faster.  Background work
-    // keeps the one-wave kernel: the two-wave kernel spends two waves per 64
-    // chunks to shorten each chain, about 1.3x the CU time per byte.
-    if (choice == 1 || (choice == 0 && (background || n_slots > 64 * kMaxPairs * cus))) return 1;
+    // the two-wave kernels while every CU holds one workgroup at most: 64
+    // KiB chunks take 1.31 ms up to 64 per CU and 1.70 up to 128, against 2.69
+    // with the one-wave kernel; with more, two workgroups share a CU and the
+    // one-wave kernel is faster.  Background work keeps the one-wave kernel:
+    // shorter chains cost more instructions, about 1.4x the CU time per byte.
+    if (choice == 1 || (choice == 0 && (background || n_slots > 128 * cus))) return 1;
     return choice == 3 || n_slots > 64 * cus ? 3 : 2;
 }
 
@@ -303,13 +367,13 @@ hipError_t launch_sha256_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t o
 }
 
 hipError_t launch_sha256_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
-                               bool two_pairs, hipStream_t s) {
+                               bool two_groups, hipStream_t s) {
     for (uint64_t base = 0; base < n_slots; base += kMaxSlotsPerLaunch) {
         const uint64_t n = n_slots - base < kMaxSlotsPerLaunch ? n_slots - base : kMaxSlotsPerLaunch;
-        if (!two_pairs)
-            sha256_split_kernel<1><<<(unsigned)((n + 63) / 64), 128, 0, s>>>(desc + base, n, out_bound, digests);
+        if (!two_groups)
+            sha256_chain_kernel<1><<<(unsigned)((n + 63) / 64), 256, 0, s>>>(desc + base, n, out_bound, digests);
         else
-            sha256_split_kernel<2><<<(unsigned)((n + 127) / 128), 256, 0, s>>>(desc + base, n, out_bound, digests);
+            sha256_chain_kernel<2><<<(unsigned)((n + 127) / 128), 512, 0, s>>>(desc + base, n, out_bound, digests);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
