@@ -42,7 +42,33 @@ HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves) {
     L.hist = c.take<uint64_t>(hv::kSortBuckets);
     L.desc = c.take<hv::LeafDesc>(n_leaves);
     L.bytes = c.used;
+    L.tape = hv::Tape{};
+    if (tape_worth(n_msgs, n_leaves)) {
+        L.tape.head = c.take<uint64_t>((size_t)n_msgs / 64 + 4);  // at most n_msgs tails, and two mixed groups
+        L.tape.ready = c.take<uint32_t>(hv::kTapeMaxWaves);
+        L.tape.states = c.take<uint8_t>(hv::kTapeMaxWaves * hv::kTapeStateBytes);
+    }
+    L.tape_bytes = c.used;
     return L;
+}
+
+hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,
+                         uint64_t n_leaves, uint8_t* digests, hipStream_t stream) {
+    const bool sha384 = alg == HV_SHA384;
+    if (tape && chunk_bytes > 0 && tape_worth(n_msgs, n_leaves) && hv::leaf_kernel_for(n_leaves, false) == 1) {
+        hv::Tape t = L.tape;
+        t.waves = hv::tape_waves(n_leaves);
+        t.full_len = sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1;
+        if (t.waves > 0) {
+            const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
+                                                      n_msgs, t, stream);
+            if (e != hipSuccess) return e;
+            return sha384 ? hv::launch_sha384_tape(L.desc, n_leaves, n_leaves, digests, t, stream)
+                          : hv::launch_sha256_tape(L.desc, n_leaves, n_leaves, digests, t, stream);
+        }
+    }
+    return sha384 ? hv::launch_sha384_auto(L.desc, n_leaves, n_leaves, digests, stream)
+                  : hv::launch_sha256_auto(L.desc, n_leaves, n_leaves, digests, stream);
 }
 
 namespace {
@@ -487,8 +513,8 @@ hv_status hash_chunks_into(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint
     if (n_leaves == 0) return up.wait(HV_OK);
 
     if (events && (st = leaf_timing_start(stream)) != HV_OK) return up.wait(st);
-    const hipError_t e = alg == HV_SHA384 ? hv::launch_sha384_auto(L.desc, n_leaves, n_leaves, leaf_digests, stream)
-                                          : hv::launch_sha256_auto(L.desc, n_leaves, n_leaves, leaf_digests, stream);
+    const hipError_t e = launch_leaves(alg, L, workspace_bytes >= L.tape_bytes, n_msgs, chunk_bytes, n_leaves,
+                                       leaf_digests, stream);
     if (e != hipSuccess) return up.wait(hip_fail(e, "leaf kernel"));
     return up.wait(events ? leaf_timing_stop(stream) : HV_OK);
 }
@@ -510,7 +536,7 @@ size_t hv_hash_workspace_bytes(uint32_t n_msgs, uint64_t n_leaves) {
         (void)fail(HV_ERR_INVALID_ARG, "%llu leaves exceed the per-call limit", (unsigned long long)n_leaves);
         return 0;
     }
-    return hash_layout(nullptr, n_msgs, n_leaves).bytes;
+    return hash_layout(nullptr, n_msgs, n_leaves).tape_bytes;
 }
 
 hv_status hv_hash_chunks_alg(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_bytes,

@@ -44,9 +44,29 @@ struct HashLayout {
     uint64_t* hist;
     hv::LeafDesc* desc;
     size_t bytes;
+    // beyond `bytes`, where a balanced leaf launch may pay (tape_worth): its
+    // scratch.  tape_bytes is the end of it (`bytes` where there is none); a
+    // workspace that ends sooner is enough, and the plain launch runs.
+    hv::Tape tape;
+    size_t tape_bytes;
 };
 
 HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves);
+
+// Calls for which the leaf table's work may be split evenly over the resident
+// waves (balance.h): more than one wave per SIMD (256 CUs), up to 16 (beyond
+// that a partly filled last round is at most a few percent, and the scratch
+// would not fit beside the table in hv_hash_chunks_noalloc's array), and few
+// messages per leaf, so that nearly all chunks are full ones when the call
+// has a chunk size at all.
+inline bool tape_worth(uint32_t n_msgs, uint64_t n_leaves) {
+    return n_leaves > 65536 && n_leaves <= (1u << 20) && n_msgs <= n_leaves / 4;
+}
+
+// The leaf kernel of a scheduled table (L.desc, L.off): the automatic choice,
+// over a tape where `tape` (L's tape scratch is there) and it pays.
+hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,
+                         uint64_t n_leaves, uint8_t* digests, hipStream_t stream);
 
 // Records a detail string for hv_last_error() and returns st.
 hv_status fail(hv_status st, const char* fmt, ...);

@@ -26,6 +26,18 @@ struct MsgDesc {
     uint64_t nbytes;
 };
 
+// Scratch of a balanced leaf launch (balance.h): the table's work as one tape,
+// cut into an interval per wave.  All pointers are device memory.
+struct Tape {
+    uint64_t* head;     // full groups, then the tape position of every other group of 64 slots, and its end
+    uint32_t* ready;    // per wave: its saved states may be read
+    uint8_t* states;    // per wave: kTapeStateBytes
+    uint64_t full_len;  // blocks of a full chunk, padding included
+    uint32_t waves;     // a multiple of 4
+};
+constexpr uint64_t kTapeStateBytes = 64 * 64;
+constexpr uint32_t kTapeMaxWaves = 3 * 1024;  // three per SIMD of 256 CUs
+
 // Per-message counts / offsets: x = full chunks, y = tail leaves (0 or 1).
 using Pair = ulonglong2;
 
@@ -45,6 +57,20 @@ hipError_t launch_sched_full(const MsgDesc* msgs, const Pair* off, uint32_t n, u
                              LeafDesc* desc, hipStream_t s);
 hipError_t launch_sched_tails(const MsgDesc* msgs, const Pair* off, uint32_t n, uint64_t C, uint64_t n_full,
                               uint64_t* hist, LeafDesc* desc, hipStream_t s);
+
+// Lays a scheduled leaf table (full chunks first, then tails by falling block
+// class) out as a tape for t.waves waves and clears t.ready; off[n_msgs].x is
+// the number of full chunks.
+hipError_t launch_tape_plan(int alg, const LeafDesc* desc, uint64_t n_slots, const Pair* off, uint32_t n_msgs,
+                            const Tape& t, hipStream_t s);
+// The one-wave leaf kernels over a planned tape.
+hipError_t launch_sha256_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
+                              const Tape& t, hipStream_t s);
+hipError_t launch_sha384_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
+                              const Tape& t, hipStream_t s);
+// Waves of the tape that a one-wave call over n_slots leaves, nearly all of
+// them full chunks, is cut into; 0 where the plain launch is as fast.
+uint32_t tape_waves(uint64_t n_slots);
 
 // SHA-384 of the n_slots leaves of a leaf table (sha384_leaves.hip): 48-byte
 // digests at digests + 48 * desc.out for desc.out < out_bound.

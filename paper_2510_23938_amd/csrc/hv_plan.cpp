@@ -27,7 +27,7 @@ PlanMem plan_mem(void* mem, uint32_t n_msgs, uint64_t n_leaves, const size_t row
     PlanMem P;
     P.hash = hash_layout(mem, n_msgs, n_leaves);
     Carver c(mem);
-    c.used = P.hash.bytes;
+    c.used = P.hash.tape_bytes;
     P.table[0] = c.take<uint64_t>(rows[0]);
     P.table[1] = c.take<uint64_t>(rows[1]);
     P.ping = c.take<uint8_t>(scratch * D);
@@ -187,9 +187,7 @@ hv_status hv_plan_run(const hv_verify_plan* plan, uint8_t* leaf_digests, uint8_t
     hipError_t e;
     if (plan->n_leaves > 0) {
         if ((st = leaf_timing_start(stream)) != HV_OK) return st;
-        e = plan->alg == HV_SHA384
-                ? hv::launch_sha384_auto(P.hash.desc, plan->n_leaves, plan->n_leaves, leaf_digests, stream)
-                : hv::launch_sha256_auto(P.hash.desc, plan->n_leaves, plan->n_leaves, leaf_digests, stream);
+        e = launch_leaves(plan->alg, P.hash, true, plan->n_msgs, plan->chunk_bytes, plan->n_leaves, leaf_digests, stream);
         if (e != hipSuccess) return hip_fail(e, "leaf kernel");
         if ((st = leaf_timing_stop(stream)) != HV_OK) return st;
     }

@@ -287,6 +287,41 @@ __global__ void __launch_bounds__(kThreads) range_select_kernel(const MsgDesc* _
     }
 }
 
+// Most blocks of a chunk in the class of an n-byte chunk (block_bytes 64 or
+// 128, pad: the 0x80 byte and the length field).
+__device__ __forceinline__ uint64_t class_blocks(uint64_t n, uint32_t block_bytes, uint32_t pad) {
+    uint64_t b = sha_blocks(n);  // the class is one of SHA-256 blocks
+    if (b >= 2048) {
+        const int e = 63 - __clzll((long long)b);
+        b = (((b >> (e - 5)) + 1) << (e - 5)) - 1;
+    }
+    return (64 * b - 9 + pad + block_bytes - 1) / block_bytes;  // 64 b - 9: the longest such chunk
+}
+
+// The tape of a balanced leaf launch (one block): the table is sorted by
+// falling class, so a group's first slot bounds its blocks.
+__global__ void __launch_bounds__(kThreads) tape_plan_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                             const Pair* __restrict__ total, uint32_t block_bytes,
+                                                             uint32_t pad, Tape t) {
+    for (uint32_t w = threadIdx.x; w < t.waves; w += kThreads) t.ready[w] = 0;
+    const uint64_t full = total->x / 64, tails = (n_slots + 63) / 64 - full;
+    const uint64_t per = (tails + kThreads - 1) / kThreads;
+    const uint64_t lo = threadIdx.x * per < tails ? threadIdx.x * per : tails;
+    const uint64_t hi = lo + per < tails ? lo + per : tails;
+    uint64_t s = 0;
+    for (uint64_t i = lo; i < hi; ++i) s += class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
+    Pair sum;
+    uint64_t at = full * t.full_len + block_exclusive_scan(make_ulonglong2(s, 0), &sum).x;
+    for (uint64_t i = lo; i < hi; ++i) {
+        t.head[1 + i] = at;
+        at += class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
+    }
+    if (threadIdx.x == 0) {
+        t.head[0] = full;
+        t.head[1 + tails] = full * t.full_len + sum.x;
+    }
+}
+
 unsigned grid_for(uint64_t n) {
     const uint64_t blocks = (n + kThreads - 1) / kThreads;
     const uint64_t cap = 65536;  // grid-stride loops cover the rest
@@ -335,6 +370,13 @@ hipError_t launch_sched_select(const MsgDesc* msgs, const Pair* off, uint32_t n,
 hipError_t launch_sched_range(const MsgDesc* msgs, const Pair* off, uint32_t n, uint64_t C, uint64_t first,
                               uint64_t k, LeafDesc* desc, uint64_t* reset, hipStream_t s) {
     range_select_kernel<<<grid_for(k), kThreads, 0, s>>>(msgs, off, n, C, first, k, desc, reset);
+    return hipGetLastError();
+}
+
+hipError_t launch_tape_plan(int alg, const LeafDesc* desc, uint64_t n_slots, const Pair* off, uint32_t n_msgs,
+                            const Tape& t, hipStream_t s) {
+    tape_plan_kernel<<<1, kThreads, 0, s>>>(desc, n_slots, off + n_msgs, alg == kAlgSha384 ? 128 : 64,
+                                            alg == kAlgSha384 ? 17 : 9, t);
     return hipGetLastError();
 }
 

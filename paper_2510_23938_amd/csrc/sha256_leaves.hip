@@ -23,6 +23,7 @@
 // Memory safety at tails: the final partial block is read with aligned dword
 // loads that each contain at least one byte of the chunk, so no access
 // touches a page the chunk does not touch; bytes past the end are masked off.
+#include "balance.h"
 #include "hv_kernels.h"
 #include "sha256_device.h"
 
@@ -56,7 +57,10 @@ __device__ __forceinline__ void wait_lgkm_all() { __builtin_amdgcn_s_waitcnt(0xC
 // blocks (at most 2^31 under the library's chunk-size limit, so the block
 // counts below cannot wrap).
 __device__ __forceinline__ void full_blocks_lds(uint32_t H[8], uint64_t src, uint32_t nfull, uint8_t* rows) {
-    const uint32_t lane = threadIdx.x & 63;
+    uint32_t lane = threadIdx.x & 63;
+    // opaque, so that in a kernel that calls this in a loop the addresses
+    // derived from it are not kept in registers across the calls
+    asm volatile("" : "+v"(lane));
     uint32_t nmax = nfull, nmin = nfull;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
@@ -173,6 +177,21 @@ __device__ __forceinline__ void final_blocks(uint32_t H[8], const uint8_t* p, ui
     }
 }
 
+// Blocks [from, to) of a wave's 64 chunks, one per lane: H starts from the
+// initial value or from saved states (from > 0); with `last`, the rest of the
+// chunk and its padding, whatever its length.
+__device__ __forceinline__ void hash_blocks(uint32_t H[8], const LeafDesc& d, uint32_t from, uint32_t to, bool last,
+                                            uint8_t* rows) {
+    const uint8_t* p = reinterpret_cast<const uint8_t*>(d.src);
+    const uint32_t nfull = (uint32_t)(d.nbytes >> 6);
+    const uint32_t f0 = from < nfull ? from : nfull, f1 = last || to > nfull ? nfull : to;
+    if (__all((d.src & 15) == 0))
+        full_blocks_lds(H, d.src + ((uint64_t)f0 << 6), f1 - f0, rows);
+    else
+        full_blocks_any(H, p + ((uint64_t)f0 << 6), f1 - f0);
+    if (last) final_blocks(H, p + ((uint64_t)nfull << 6), (uint32_t)(d.nbytes & 63), d.nbytes);
+}
+
 __global__ void __launch_bounds__(kThreads) sha256_leaves_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
                                                                  uint64_t out_bound, uint8_t* __restrict__ digests) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
@@ -180,22 +199,44 @@ __global__ void __launch_bounds__(kThreads) sha256_leaves_kernel(const LeafDesc*
     const bool live = slot < n_slots;
     LeafDesc d = {0, 0, 0};
     if (live) d = desc[slot];
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(d.src);
-    const uint32_t nfull = (uint32_t)(d.nbytes >> 6);
-
     uint32_t H[8];
     init_state(H);
-    if (__all((d.src & 15) == 0)) {
-        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        full_blocks_lds(H, d.src, nfull, stage[wave]);
-    } else {
-        full_blocks_any(H, p, nfull);
-    }
-    final_blocks(H, p + ((uint64_t)nfull << 6), (uint32_t)(d.nbytes & 63), d.nbytes);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    hash_blocks(H, d, 0, 0, true, stage[wave]);
     if (live && d.out < out_bound) store_digest(digests + 32 * d.out, H);
 }
 
+// The same over the intervals of a tape (balance.h), one per wave.
+__global__ void __launch_bounds__(kThreads, 3) sha256_tape_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                               uint64_t out_bound, uint8_t* __restrict__ digests,
+                                                               const Tape tape) {
+    __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
+    const uint32_t in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave = blockIdx.x * kWaves + in_block;
+    TapeWalk walk(tape, n_slots, wave);
+    Piece piece;
+    while (walk.next(&piece)) {
+        const uint64_t slot = 64 * piece.group + (threadIdx.x & 63);
+        LeafDesc d = {0, 0, 0};
+        if (slot < n_slots) d = desc[slot];
+        uint32_t H[8];
+        if (piece.from > 0 && !load_states<8>(tape, wave, H)) piece.from = 0;
+        if (piece.from == 0) init_state(H);
+        hash_blocks(H, d, piece.from, piece.to, piece.last, stage[in_block]);
+        if (!piece.last)
+            save_states<8>(tape, wave, H);
+        else if (slot < n_slots && d.out < out_bound)
+            store_digest(digests + 32 * d.out, H);
+    }
+}
+
 }  // namespace
+
+hipError_t launch_sha256_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
+                              const Tape& tape, hipStream_t s) {
+    sha256_tape_kernel<<<tape.waves / kWaves, kThreads, 0, s>>>(desc, n_slots, out_bound, digests, tape);
+    return hipGetLastError();
+}
 
 hipError_t launch_sha256_leaves(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                                 hipStream_t s) {

@@ -359,6 +359,27 @@ int leaf_kernel_for(uint64_t n_slots, bool background) {
     return choice == 3 || n_slots > 64 * cus ? 3 : 2;
 }
 
+uint32_t tape_waves(uint64_t n_slots) {
+    // In units of a wave's time when a SIMD is full: one wave alone on a SIMD
+    // takes 1.10 (64 KiB chunks: 2.72 ms), two 2.04 (5.06), three 3 (7.44), and
+    // a fourth waits for one of them.  x waves per SIMD run plainly as threes
+    // and a remainder; on a tape, as w at once (at most x: an interval is no
+    // shorter than a chunk), each x / w long.
+    static constexpr double kAtOnce[4] = {0, 1.10, 2.04, 3.0};
+    const uint32_t simds = 4 * device_cus();
+    if (simds == 0 || 3 * simds > kTapeMaxWaves) return 0;
+    const double x = (double)n_slots / 64 / simds;
+    const uint64_t whole = (n_slots + 64 * (uint64_t)simds - 1) / (64 * (uint64_t)simds);
+    double best = ((double)(whole / 3 * 3) + kAtOnce[whole % 3]) * 0.985;  // the walk's own cost
+    uint32_t waves = 0;
+    for (uint32_t w = 1; w <= 3 && w <= x; ++w)
+        if (x / w * kAtOnce[w] < best) {
+            best = x / w * kAtOnce[w];
+            waves = w * simds;
+        }
+    return waves;
+}
+
 hipError_t launch_sha256_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background) {
     const int k = leaf_kernel_for(n_slots, background);

@@ -8,6 +8,7 @@
 // big-endian bit length, in one final block when the tail is at most 111
 // bytes, else two.  Tail reads are aligned dwords that each hold at least one
 // chunk byte, as in the SHA-256 kernel.
+#include "balance.h"
 #include "hv_kernels.h"
 #include "sha384_device.h"
 
@@ -34,7 +35,8 @@ __device__ __forceinline__ void block_from(const uint4 r[8], uint64_t W[16]) {
 // Whole 128-byte blocks of the wave's 64 chunks (all 16-byte aligned), staged
 // through this wave's 8 KB LDS rows; nfull <= 2^30 (the chunk-size limit).
 __device__ __forceinline__ void full_blocks_lds(uint64_t H[8], uint64_t src, uint32_t nfull, uint8_t* rows) {
-    const uint32_t lane = threadIdx.x & 63;
+    uint32_t lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // as in the SHA-256 kernel
     uint32_t nmax = nfull, nmin = nfull;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
@@ -144,6 +146,19 @@ __device__ __forceinline__ void final_blocks(uint64_t H[8], const uint8_t* p, ui
     }
 }
 
+// Blocks [from, to) of a wave's 64 chunks, as in the SHA-256 kernel.
+__device__ __forceinline__ void hash_blocks(uint64_t H[8], const LeafDesc& d, uint32_t from, uint32_t to, bool last,
+                                            uint8_t* rows) {
+    const uint8_t* p = reinterpret_cast<const uint8_t*>(d.src);
+    const uint32_t nfull = (uint32_t)(d.nbytes >> 7);
+    const uint32_t f0 = from < nfull ? from : nfull, f1 = last || to > nfull ? nfull : to;
+    if (__all((d.src & 15) == 0))
+        full_blocks_lds(H, d.src + ((uint64_t)f0 << 7), f1 - f0, rows);
+    else
+        full_blocks_any(H, p + ((uint64_t)f0 << 7), f1 - f0);
+    if (last) final_blocks(H, p + ((uint64_t)nfull << 7), (uint32_t)(d.nbytes & 127), d.nbytes);
+}
+
 __global__ void __launch_bounds__(kThreads) sha384_leaves_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
                                                                  uint64_t out_bound, uint8_t* __restrict__ digests) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
@@ -151,22 +166,56 @@ __global__ void __launch_bounds__(kThreads) sha384_leaves_kernel(const LeafDesc*
     const bool live = slot < n_slots;
     LeafDesc d = {0, 0, 0};
     if (live) d = desc[slot];
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(d.src);
-    const uint32_t nfull = (uint32_t)(d.nbytes >> 7);
-
     uint64_t H[8];
     init_state384(H);
-    if (__all((d.src & 15) == 0)) {
-        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        full_blocks_lds(H, d.src, nfull, stage[wave]);
-    } else {
-        full_blocks_any(H, p, nfull);
-    }
-    final_blocks(H, p + ((uint64_t)nfull << 7), (uint32_t)(d.nbytes & 127), d.nbytes);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    hash_blocks(H, d, 0, 0, true, stage[wave]);
     if (live && d.out < out_bound) store_digest384(digests + 48 * d.out, H);
 }
 
+// The same over the intervals of a tape (balance.h), one per wave.
+__global__ void __launch_bounds__(kThreads, 3) sha384_tape_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                                  uint64_t out_bound, uint8_t* __restrict__ digests,
+                                                                  const Tape tape) {
+    __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
+    const uint32_t in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave = blockIdx.x * kWaves + in_block;
+    TapeWalk walk(tape, n_slots, wave);
+    Piece piece;
+    while (walk.next(&piece)) {
+        const uint64_t slot = 64 * piece.group + (threadIdx.x & 63);
+        LeafDesc d = {0, 0, 0};
+        if (slot < n_slots) d = desc[slot];
+        uint64_t H[8];
+        uint32_t words[16];
+        if (piece.from > 0 && !load_states<16>(tape, wave, words)) piece.from = 0;
+        if (piece.from == 0) {
+            init_state384(H);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) H[i] = pack(words[2 * i + 1], words[2 * i]);
+        }
+        hash_blocks(H, d, piece.from, piece.to, piece.last, stage[in_block]);
+        if (!piece.last) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                words[2 * i] = lo32(H[i]);
+                words[2 * i + 1] = hi32(H[i]);
+            }
+            save_states<16>(tape, wave, words);
+        } else if (slot < n_slots && d.out < out_bound) {
+            store_digest384(digests + 48 * d.out, H);
+        }
+    }
+}
+
 }  // namespace
+
+hipError_t launch_sha384_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
+                              const Tape& t, hipStream_t s) {
+    sha384_tape_kernel<<<t.waves / kWaves, kThreads, 0, s>>>(desc, n_slots, out_bound, digests, t);
+    return hipGetLastError();
+}
 
 hipError_t launch_sha384_leaves(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                                 hipStream_t s) {
