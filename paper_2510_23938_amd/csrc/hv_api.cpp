@@ -261,9 +261,16 @@ MerkleLayout merkle_layout(void* ws, uint64_t n_nodes, uint32_t n_seg, uint32_t 
 namespace hvh {
 
 uint64_t merkle_tiles_bound(uint64_t n_nodes, uint32_t n_seg) {
-    // a launch over c entries of a segment writes max(1, ceil(c / w)) <= c / w + 1 nodes
-    const uint64_t w = merkle_grouped(n_nodes) ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
-    return n_nodes / w + (uint64_t)n_seg + 1;
+    // a launch over c entries of a segment writes max(1, ceil(c / w)) <= c / w + 1
+    // nodes; a group launch by the second rule has at most 8 n_seg entries (so
+    // that the bound never falls as n_nodes grows, those are counted beyond that too)
+    const uint64_t w = n_nodes >= kGroupMinNodes ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
+    uint64_t out = n_nodes / w;
+    if (n_seg > kManySegments) {
+        const uint64_t few = n_nodes < 8 * (uint64_t)n_seg ? n_nodes : 8 * (uint64_t)n_seg;
+        if (few / hv::kGroupNodes > out) out = few / hv::kGroupNodes;
+    }
+    return out + (uint64_t)n_seg + 1;
 }
 
 hv_status check_segments(const uint64_t* seg_offsets, uint32_t n_seg) {
@@ -284,7 +291,7 @@ hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, std::vector<u
     int k = 0;
     for (;;) {
         const uint64_t entries = (*table)[(size_t)k * row + n_seg];
-        const uint64_t w = merkle_width(entries);
+        const uint64_t w = merkle_width(entries, n_seg, k + 1);
         std::vector<uint64_t> next(row);
         next[0] = 0;
         bool more = false;
@@ -340,7 +347,7 @@ hv_status merkle_launch_kinds(hv_alg alg, const uint64_t* seg_offsets, uint32_t 
     const size_t row = (size_t)n_seg + 1;
     for (int k = 1; k <= *launches; ++k) {
         const uint64_t entries = table[(size_t)(k - 1) * row + n_seg], out = table[(size_t)k * row + n_seg];
-        const bool grouped = merkle_grouped(entries);
+        const bool grouped = merkle_grouped(entries, n_seg, k);
         kind[k - 1] = grouped ? 1 : 2;
         units[k - 1] = out;
         one_lane[k - 1] = grouped ? merkle_group_main(out, k == 1, alg == HV_SHA384, cus) : 0;
@@ -360,7 +367,7 @@ hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64
         const uint64_t* out_off = table + (size_t)k * row;
         const uint64_t entries = k == 1 ? n_nodes : outputs[k - 2];  // the plan's rule, from the same counts
         hipError_t e;
-        if (merkle_grouped(entries)) {
+        if (merkle_grouped(entries, n_seg, k)) {
             if (cus == 0 && (e = stream_cus(stream, &cus)) != hipSuccess) return hip_fail(e, "device query");
             const uint64_t n_main = merkle_group_main(outputs[k - 1], k == 1, alg == HV_SHA384, cus);
             e = hv::launch_merkle_groups(a, in, dst, in_off, out_off, n_seg, outputs[k - 1], n_main, k == 1, stream);

@@ -89,25 +89,37 @@ hv_status hash_chunks_into(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint
 hv_status queue_schedule(const hv::MsgDesc* msgs_dev, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_full,
                          uint64_t n_leaves, const HashLayout& L, hipStream_t stream);
 
-// Segmented Merkle reductions chain launches.  A launch whose input has at
-// least kGroupMinNodes entries is a group launch (3 levels in registers, one
-// lane per group of 8 entries: every lane busy on the widest levels); every
-// other launch takes 9 levels (512-node tiles).  Up to 2^31 entries (the
-// per-call limit) that is at most 5 group launches and 2 tile launches.
+// Segmented Merkle reductions chain launches, each a group launch (3 levels in
+// registers, one or four lanes per group of 8 entries) or a tile launch (9
+// levels, a workgroup per 512-node tile).  Launch k (from 1) over `entries`
+// nodes in n_seg segments is a group launch
+//   - from kGroupMinNodes entries on, where the widest levels keep every lane
+//     busy, or
+//   - for more than kManySegments segments of at most 8 entries on average:
+//     a tile is a workgroup however few nodes it has, three at a time on a CU,
+//     and reduces them at one wave's latency (20,000 segments of 1 to 13
+//     entries: 886 us), while a group is a lane or four (two launches, see
+//     merkle_group_main: 40 us).  Only the first three launches, so that a few
+//     long segments among the short ones still get tiles.
+// Up to 2^31 entries (the per-call limit) that is at most 5 group launches and
+// 2 tile launches, or 3 and 3.
 constexpr int kMaxMerkleLaunches = 8;
 constexpr uint64_t kGroupMinNodes = (uint64_t)1 << 18;
-inline bool merkle_grouped(uint64_t n_nodes) { return n_nodes >= kGroupMinNodes; }
-// Entries one output node of a launch over n_nodes entries covers.
-inline uint64_t merkle_width(uint64_t n_nodes) {
-    return merkle_grouped(n_nodes) ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
+constexpr uint32_t kManySegments = 1536;  // two rounds of tiles on 256 CUs
+inline bool merkle_grouped(uint64_t entries, uint32_t n_seg, int k) {
+    return entries >= kGroupMinNodes || (k <= 3 && n_seg > kManySegments && entries <= 8 * (uint64_t)n_seg);
+}
+// Entries one output node of such a launch covers.
+inline uint64_t merkle_width(uint64_t entries, uint32_t n_seg, int k) {
+    return merkle_grouped(entries, n_seg, k) ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
 }
 
 // Host plan of a segmented Merkle reduction over validated segment offsets:
 // `table` gets rows of n_seg + 1 offsets -- row 0 the segment offsets, row k
 // the first output node of each segment after launch k (a segment with c
 // nodes gets max(1, ceil(c / w)) outputs, w = merkle_width(entries of row
-// k - 1)) -- and `launches` the launch count.  Launch k is a group launch
-// exactly when merkle_grouped(entries of row k - 1).
+// k - 1, n_seg, k)) -- and `launches` the launch count.  Launch k is a group
+// launch exactly when merkle_grouped(entries of row k - 1, n_seg, k).
 hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, std::vector<uint64_t>* table, int* launches);
 
 // Segment offsets: start at 0, never decrease, at most the per-call entry limit.
@@ -134,7 +146,7 @@ inline uint64_t merkle_group_main(uint64_t n_groups, bool leaf_mode, bool sha384
     const uint64_t D = 8 * leaf + 7 * node, d = 2 * leaf + 3 * node;
     const uint64_t R = 256 * (uint64_t)cus;
     const uint64_t k = n_groups / R, r = n_groups % R;
-    if (k == 0 || r == 0) return n_groups;
+    if (r == 0) return n_groups;
     const uint64_t all = (k + 1) * D, split = k * D + (4 * r + R - 1) / R * d;
     return split < all ? k * R : n_groups;
 }
