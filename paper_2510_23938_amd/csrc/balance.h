@@ -42,12 +42,12 @@ struct TapeWalk {
     const uint64_t* tail_start;  // tape position of each group with a tail, and the tape's end
     uint64_t full_groups;        // the groups of full chunks only, the table's first
     uint64_t full_len;           // blocks of each of them
-    uint32_t tail_groups;        // the others
+    uint64_t group, start;       // the group `pos` lies in, and its tape position
     uint64_t pos, end;           // what is left of the interval
 
     __device__ __forceinline__ TapeWalk(const Tape& t, uint64_t n_slots, uint32_t wave)
-        : tail_start(t.head + 1), full_groups(t.head[0]), full_len(t.full_len),
-          tail_groups((uint32_t)((n_slots + 63) / 64 - full_groups)) {
+        : tail_start(t.head + 1), full_groups(t.head[0]), full_len(t.full_len) {
+        const uint32_t tail_groups = (uint32_t)((n_slots + 63) / 64 - full_groups);
         const uint64_t total = tail_start[tail_groups];
         uint64_t share = (total + t.waves - 1) / t.waves;
         // the longest group is a full one or the first of the others (theirs
@@ -57,33 +57,34 @@ struct TapeWalk {
         share = share > longest ? share : longest;
         pos = share * (t.waves - 1 - wave);
         end = pos + share < total ? pos + share : total;
+        if (pos < full_groups * full_len) {
+            group = pos / full_len;
+            start = group * full_len;
+        } else {
+            uint32_t lo = 0, hi = tail_groups;  // tail_start[lo] <= pos < tail_start[hi], or pos >= end
+            while (hi > lo + 1) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if (tail_start[mid] <= pos) lo = mid; else hi = mid;
+            }
+            group = full_groups + lo;
+            start = tail_start[lo];
+        }
     }
 
     __device__ __forceinline__ bool next(Piece* p) {
         if (pos >= end) return false;
-        uint64_t start, len;
-        const uint64_t full = full_groups * full_len;
-        if (pos < full) {
-            p->group = pos / full_len;
-            start = p->group * full_len;
-            len = full_len;
-        } else {
-            uint32_t lo = 0, hi = tail_groups;  // tail_start[lo] <= pos < tail_start[hi]
-            while (hi - lo > 1) {
-                const uint32_t mid = lo + (hi - lo) / 2;
-                if (tail_start[mid] <= pos) lo = mid; else hi = mid;
-            }
-            p->group = full_groups + lo;
-            start = tail_start[lo];
-            len = tail_start[lo + 1] - start;
-        }
+        const uint64_t len =
+            group < full_groups ? full_len : tail_start[group - full_groups + 1] - tail_start[group - full_groups];
         const uint64_t left = pos - start;                                 // of the group, in the interval before
         const uint64_t here = start + len < end ? len - left : end - pos;  // of the group, in this one
+        p->group = group;
         // at the interval's start the group's first blocks; at its end the last ones
         p->last = left == 0;
         p->from = p->last ? (uint32_t)(len - here) : 0u;
         p->to = p->from + (uint32_t)here;
         pos += here;
+        start += len;
+        ++group;
         return true;
     }
 };

@@ -17,8 +17,9 @@
 // a chunk's row are XOR-swizzled by chunk index so that the 64 lanes reading
 // their own rows with ds_read_b128 hit distinct banks.  A stage is copied to
 // VGPRs before the next stage's loads are issued into the same buffer, so
-// the loads run under the two compressions of the current stage.  Chunks
-// that are not 16-byte aligned take a dword-gather path instead.
+// the loads run under the two compressions of the current stage.  A wave with
+// a chunk that is not 16-byte aligned stages the aligned bytes around its
+// chunks the same way and shifts them into place in registers.
 //
 // Memory safety at tails: the final partial block is read with aligned dword
 // loads that each contain at least one byte of the chunk, so no access
@@ -139,14 +140,97 @@ __device__ __forceinline__ void gather_words(const uint8_t* p, uint32_t valid, u
     for (int i = 0; i < 16; ++i) X[i] = __builtin_amdgcn_alignbyte(D[i + 1], D[i], sh);
 }
 
-// Whole blocks from a chunk at any alignment.
-__device__ __forceinline__ void full_blocks_any(uint32_t H[8], const uint8_t* p, uint32_t nfull) {
-    for (uint32_t b = 0; b < nfull; ++b) {
-        uint32_t W[16];
-        gather_words(p + 64 * (uint64_t)b, 64, W);
+// One block's 16 message words from the 20 dwords D in which it starts `shift`
+// = 0..15 bytes in: two rounds of masked selects for whole dwords, and one byte
+// permute per word that also puts the bytes in order (sel).
+__device__ __forceinline__ void shifted_words(const uint32_t* D, uint32_t by_two, uint32_t by_one, uint32_t sel,
+                                              uint32_t W[16]) {
+    uint32_t X[18];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) W[i] = bswap(W[i]);
-        compress(H, W);
+    for (int i = 0; i < 18; ++i) X[i] = choose(by_two, D[i + 2], D[i]);
+#pragma unroll
+    for (int i = 0; i < 17; ++i) X[i] = choose(by_one, X[i + 1], X[i]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) W[i] = __builtin_amdgcn_perm(X[i + 1], X[i], sel);
+}
+
+// Whole blocks of the wave's 64 chunks at any alignment, on the staging of
+// full_blocks_lds: a stage is the eight 16-byte granules 8s + 1..8s + 8 of each
+// chunk, counted from the granule its first byte lies in, and the last one
+// read stays in registers as the first of the next stage.  A granule is loaded
+// only if it holds a byte of a whole block.  The realignment adds 35
+// operations to a block's 1405 (byte order included in both); a gather of each
+// lane's own dwords, 17 loads of 64 lines per block, was bound by those loads
+// instead.
+__device__ __forceinline__ void full_blocks_any(uint32_t H[8], uint64_t src, uint32_t nfull, uint8_t* rows) {
+    uint32_t lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // as in full_blocks_lds
+    const uint32_t shift = (uint32_t)src & 15;
+    uint4 first = make_uint4(0, 0, 0, 0);
+    if (nfull > 0) first = *reinterpret_cast<const uint4*>(src - shift);
+    const uint8_t* from[kRowsPerLoad];
+    uint32_t until[kRowsPerLoad];  // stages in which that slot holds a byte of a whole block
+    uint32_t nmax = nfull, all = 0xffffffffu;
+#pragma unroll
+    for (int j = 0; j < kRowsPerLoad; ++j) {
+        const uint32_t c = kRowsPerLoad * j + (lane >> 3);
+        const uint32_t at = 16 * (1 + ((lane & 7) ^ swizzle(c)));
+        const uint64_t s = __shfl(src, (int)c);
+        const uint64_t end = (s & 15) + 64 * (uint64_t)__shfl(nfull, (int)c);
+        from[j] = reinterpret_cast<const uint8_t*>(s & ~(uint64_t)15) + at;
+        until[j] = end > at ? (uint32_t)((end - at + kStageBytes - 1) / kStageBytes) : 0u;
+        all = until[j] < all ? until[j] : all;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(all, o);
+        nmax = x > nmax ? x : nmax;
+        all = y < all ? y : all;
+    }
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    all = __builtin_amdgcn_readfirstlane(all);  // stages that every slot of every chunk takes part in
+    const uint32_t stages = (nmax + 1) / 2;
+    if (stages == 0) return;
+#pragma unroll
+    for (int j = 0; j < kRowsPerLoad; ++j)
+        if (0 < until[j]) __builtin_amdgcn_global_load_lds(from[j], rows + 1024 * j, 16, 0, 0);
+
+    const uint8_t* row = rows + kStageBytes * lane;
+    const uint32_t sw = swizzle(lane);
+    const uint32_t by_two = shift & 8 ? ~0u : 0u, by_one = shift & 4 ? ~0u : 0u;
+    const uint32_t sel = 0x00010203u + 0x01010101u * (shift & 3);
+    for (uint32_t st = 0; st < stages; ++st) {
+        wait_vm_all();  // stage st is in LDS
+        uint32_t D[36] = {first.x, first.y, first.z, first.w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint4 r = *reinterpret_cast<const uint4*>(row + 16 * (k ^ sw));
+            D[4 + 4 * k] = r.x; D[5 + 4 * k] = r.y; D[6 + 4 * k] = r.z; D[7 + 4 * k] = r.w;
+        }
+        wait_lgkm_all();  // and in VGPRs: the buffer may be refilled
+        first = make_uint4(D[32], D[33], D[34], D[35]);
+        const uint32_t nx = st + 1;
+        if (nx < stages) {
+            const uint64_t off = (uint64_t)kStageBytes * nx;
+            if (nx < all) {
+#pragma unroll
+                for (int j = 0; j < kRowsPerLoad; ++j)
+                    __builtin_amdgcn_global_load_lds(from[j] + off, rows + 1024 * j, 16, 0, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRowsPerLoad; ++j)
+                    if (nx < until[j]) __builtin_amdgcn_global_load_lds(from[j] + off, rows + 1024 * j, 16, 0, 0);
+            }
+        }
+        uint32_t W[16];
+        if (2 * st < nfull) {
+            shifted_words(D, by_two, by_one, sel, W);
+            compress(H, W);
+        }
+        if (2 * st + 1 < nfull) {
+            shifted_words(D + 16, by_two, by_one, sel, W);
+            compress(H, W);
+        }
     }
 }
 
@@ -177,56 +261,69 @@ __device__ __forceinline__ void final_blocks(uint32_t H[8], const uint8_t* p, ui
     }
 }
 
-// Blocks [from, to) of a wave's 64 chunks, one per lane: H starts from the
-// initial value or from saved states (from > 0); with `last`, the rest of the
-// chunk and its padding, whatever its length.
-__device__ __forceinline__ void hash_blocks(uint32_t H[8], const LeafDesc& d, uint32_t from, uint32_t to, bool last,
-                                            uint8_t* rows) {
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(d.src);
+// The whole blocks among blocks [from, to) of a wave's 64 chunks, one per lane;
+// with `last`, all from `from` on.
+__device__ __forceinline__ void whole_blocks(uint32_t H[8], const LeafDesc& d, uint32_t from, uint32_t to, bool last,
+                                             uint8_t* rows) {
     const uint32_t nfull = (uint32_t)(d.nbytes >> 6);
     const uint32_t f0 = from < nfull ? from : nfull, f1 = last || to > nfull ? nfull : to;
     if (__all((d.src & 15) == 0))
         full_blocks_lds(H, d.src + ((uint64_t)f0 << 6), f1 - f0, rows);
     else
-        full_blocks_any(H, p + ((uint64_t)f0 << 6), f1 - f0);
-    if (last) final_blocks(H, p + ((uint64_t)nfull << 6), (uint32_t)(d.nbytes & 63), d.nbytes);
+        full_blocks_any(H, d.src + ((uint64_t)f0 << 6), f1 - f0, rows);
+}
+
+// The rest of a wave's chunks, and their digests.
+__device__ __forceinline__ void finish(uint32_t H[8], const LeafDesc& d, bool live, uint64_t out_bound,
+                                       uint8_t* digests) {
+    const uint64_t whole = d.nbytes & ~(uint64_t)63;
+    final_blocks(H, reinterpret_cast<const uint8_t*>(d.src) + whole, (uint32_t)(d.nbytes & 63), d.nbytes);
+    if (live && d.out < out_bound) store_digest(digests + 32 * d.out, H);
+}
+
+__device__ __forceinline__ LeafDesc load_desc(const LeafDesc* __restrict__ desc, uint64_t slot, uint64_t n_slots) {
+    LeafDesc d = {0, 0, 0};
+    if (slot < n_slots) d = desc[slot];
+    return d;
 }
 
 __global__ void __launch_bounds__(kThreads) sha256_leaves_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
                                                                  uint64_t out_bound, uint8_t* __restrict__ digests) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
     const uint64_t slot = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-    const bool live = slot < n_slots;
-    LeafDesc d = {0, 0, 0};
-    if (live) d = desc[slot];
+    const LeafDesc d = load_desc(desc, slot, n_slots);
     uint32_t H[8];
     init_state(H);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    hash_blocks(H, d, 0, 0, true, stage[wave]);
-    if (live && d.out < out_bound) store_digest(digests + 32 * d.out, H);
+    whole_blocks(H, d, 0, 0, true, stage[wave]);
+    finish(H, d, slot < n_slots, out_bound, digests);
 }
 
 // The same over the intervals of a tape (balance.h), one per wave.
 __global__ void __launch_bounds__(kThreads, 3) sha256_tape_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
-                                                               uint64_t out_bound, uint8_t* __restrict__ digests,
-                                                               const Tape tape) {
+                                                                  uint64_t out_bound, uint8_t* __restrict__ digests,
+                                                                  const Tape tape) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[kWaves][64 * kStageBytes];
     const uint32_t in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t wave = blockIdx.x * kWaves + in_block;
     TapeWalk walk(tape, n_slots, wave);
     Piece piece;
     while (walk.next(&piece)) {
-        const uint64_t slot = 64 * piece.group + (threadIdx.x & 63);
-        LeafDesc d = {0, 0, 0};
-        if (slot < n_slots) d = desc[slot];
+        uint32_t lane = threadIdx.x & 63;
         uint32_t H[8];
         if (piece.from > 0 && !load_states<8>(tape, wave, H)) piece.from = 0;
         if (piece.from == 0) init_state(H);
-        hash_blocks(H, d, piece.from, piece.to, piece.last, stage[in_block]);
-        if (!piece.last)
+        whole_blocks(H, load_desc(desc, 64 * piece.group + lane, n_slots), piece.from, piece.to, piece.last,
+                     stage[in_block]);
+        if (piece.last) {
+            // read again: kept across the blocks, the descriptor's registers
+            // would cost the third wave per SIMD
+            asm volatile("" : "+v"(lane));
+            const uint64_t slot = 64 * piece.group + lane;
+            finish(H, load_desc(desc, slot, n_slots), slot < n_slots, out_bound, digests);
+        } else {
             save_states<8>(tape, wave, H);
-        else if (slot < n_slots && d.out < out_bound)
-            store_digest(digests + 32 * d.out, H);
+        }
     }
 }
 

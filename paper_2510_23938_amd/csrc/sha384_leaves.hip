@@ -106,14 +106,81 @@ __device__ __forceinline__ void gather_words(const uint8_t* p, uint32_t valid, u
     for (int i = 0; i < 32; ++i) X[i] = __builtin_amdgcn_alignbyte(D[i + 1], D[i], sh);
 }
 
-__device__ __forceinline__ void full_blocks_any(uint64_t H[8], const uint8_t* p, uint32_t nfull) {
-    for (uint32_t b = 0; b < nfull; ++b) {
-        uint32_t X[32];
-        gather_words(p + 128 * (uint64_t)b, 128, X);
-        uint64_t W[16];
+// Whole blocks of the wave's 64 chunks at any alignment, as in the SHA-256
+// kernel: a stage is the granules 8b + 1..8b + 8 of each chunk, the last one
+// read starts the next block, and selects and byte permutes shift the words
+// into place (67 operations more than a block's 3426).
+__device__ __forceinline__ void full_blocks_any(uint64_t H[8], uint64_t src, uint32_t nfull, uint8_t* rows) {
+    uint32_t lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const uint32_t shift = (uint32_t)src & 15;
+    uint4 first = make_uint4(0, 0, 0, 0);
+    if (nfull > 0) first = *reinterpret_cast<const uint4*>(src - shift);
+    const uint8_t* from[kRowsPerLoad];
+    uint32_t until[kRowsPerLoad];  // stages in which that slot holds a byte of a whole block
+    uint32_t nmax = nfull, all = 0xffffffffu;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) W[i] = be64(X[2 * i], X[2 * i + 1]);
-        compress512(H, W);
+    for (int j = 0; j < kRowsPerLoad; ++j) {
+        const uint32_t c = kRowsPerLoad * j + (lane >> 3);
+        const uint32_t at = 16 * (1 + ((lane & 7) ^ swizzle(c)));
+        const uint64_t s = __shfl(src, (int)c);
+        const uint64_t end = (s & 15) + 128 * (uint64_t)__shfl(nfull, (int)c);
+        from[j] = reinterpret_cast<const uint8_t*>(s & ~(uint64_t)15) + at;
+        until[j] = end > at ? (uint32_t)((end - at + kStageBytes - 1) / kStageBytes) : 0u;
+        all = until[j] < all ? until[j] : all;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(all, o);
+        nmax = x > nmax ? x : nmax;
+        all = y < all ? y : all;
+    }
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    all = __builtin_amdgcn_readfirstlane(all);  // stages that every slot of every chunk takes part in
+    if (nmax == 0) return;
+#pragma unroll
+    for (int j = 0; j < kRowsPerLoad; ++j)
+        if (0 < until[j]) __builtin_amdgcn_global_load_lds(from[j], rows + 1024 * j, 16, 0, 0);
+
+    const uint8_t* row = rows + kStageBytes * lane;
+    const uint32_t sw = swizzle(lane);
+    const uint32_t by_two = shift & 8 ? ~0u : 0u, by_one = shift & 4 ? ~0u : 0u;
+    const uint32_t sel = 0x00010203u + 0x01010101u * (shift & 3);
+    for (uint32_t b = 0; b < nmax; ++b) {
+        wait_vm_all();
+        uint32_t D[36] = {first.x, first.y, first.z, first.w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint4 r = *reinterpret_cast<const uint4*>(row + 16 * (k ^ sw));
+            D[4 + 4 * k] = r.x; D[5 + 4 * k] = r.y; D[6 + 4 * k] = r.z; D[7 + 4 * k] = r.w;
+        }
+        wait_lgkm_all();
+        first = make_uint4(D[32], D[33], D[34], D[35]);
+        const uint32_t nx = b + 1;
+        if (nx < nmax) {
+            const uint64_t off = (uint64_t)kStageBytes * nx;
+            if (nx < all) {
+#pragma unroll
+                for (int j = 0; j < kRowsPerLoad; ++j)
+                    __builtin_amdgcn_global_load_lds(from[j] + off, rows + 1024 * j, 16, 0, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRowsPerLoad; ++j)
+                    if (nx < until[j]) __builtin_amdgcn_global_load_lds(from[j] + off, rows + 1024 * j, 16, 0, 0);
+            }
+        }
+        if (b < nfull) {
+#pragma unroll
+            for (int i = 0; i < 34; ++i) D[i] = __builtin_amdgcn_bitop3_b32(by_two, D[i + 2], D[i], 0xCA);
+#pragma unroll
+            for (int i = 0; i < 33; ++i) D[i] = __builtin_amdgcn_bitop3_b32(by_one, D[i + 1], D[i], 0xCA);
+            uint64_t W[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                W[i] = pack(__builtin_amdgcn_perm(D[2 * i + 1], D[2 * i], sel),
+                            __builtin_amdgcn_perm(D[2 * i + 2], D[2 * i + 1], sel));
+            compress512(H, W);
+        }
     }
 }
 
@@ -155,7 +222,7 @@ __device__ __forceinline__ void hash_blocks(uint64_t H[8], const LeafDesc& d, ui
     if (__all((d.src & 15) == 0))
         full_blocks_lds(H, d.src + ((uint64_t)f0 << 7), f1 - f0, rows);
     else
-        full_blocks_any(H, p + ((uint64_t)f0 << 7), f1 - f0);
+        full_blocks_any(H, d.src + ((uint64_t)f0 << 7), f1 - f0, rows);
     if (last) final_blocks(H, p + ((uint64_t)nfull << 7), (uint32_t)(d.nbytes & 127), d.nbytes);
 }
 
