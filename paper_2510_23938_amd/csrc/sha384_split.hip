@@ -1,24 +1,41 @@
 // sha384_split.hip -- SHA-384 of every chunk for small leaf counts: the
-// two-wave form of the SHA-384 leaf kernel, on the scheme of the SHA-256 one
+// SHA-384 forms of the kernels that shorten one chunk's chain of blocks
 // (sha256_split.hip).
 //
 // A chunk is one chain of 128-byte blocks, so with fewer chunks than the chip
 // has lanes its time is that chain's latency, and a lone wave issues one
-// instruction per ~4.6 cycles.  A producer wave loads each block one block
-// ahead, builds its 16 64-bit message words (padding of FIPS 180-4 section
-// 5.1.2: tail, 0x80, zeros, 128-bit bit length) and expands them to the 80
-// schedule words (section 6.4 step 1) in a double-buffered LDS area; a
-// consumer wave runs only the 80 rounds and the feed-forward.  That moves
-// about 1250 of the 3416 operations per block off the consumer's path.
+// instruction per 4.6 to 4.9 cycles: the instructions on the wave that carries
+// the state are the time.  The one-wave kernel has 3416 per block.
 //
-// Synchronisation, exec mask and placement are as in the SHA-256 kernel: both
-// waves of a pair run the same number of barriers (the workgroup's most
-// blocks), one per block; the barrier orders LDS only; every lane runs every
-// block (dead lanes and finished chunks on zeros or stale words) and only the
-// loads, the state update and the digest store are per lane; one pair per
-// workgroup up to 64 chunks per CU, two up to 128.  The schedule takes
-// 80 x 8 bytes per lane per buffer: 80 KB per pair, so a two-pair workgroup
-// fills the CU's 160 KB of LDS.
+// Up to 64 chunks per CU: the chain kernel.  A chunk has two lanes of a
+// consumer wave, one for a..d and one for e..h, whose halves of a round are
+// one instruction stream with the a lanes two steps behind (the recurrence is
+// explained in sha256_split.hip), and two producer waves build alternate
+// blocks' 80 schedule words, each with its round constant.  On 64-bit words
+// in 32-bit halves a step is 19 instructions against 27 for a round on one
+// lane: a Sigma 8 (as rotr(x ^ rotr(x, i) ^ rotr(x, j), k), whose amounts are
+// below 32 for Sigma0 and Sigma1 alike, so that the two lanes' rotations
+// differ by a shift register only), Ch or Maj 4, -d or h + K + W 3, the
+// partner's value 2 (an addition with DPP operands) and 2 additions.  A
+// workgroup is 64 chunks, two consumers and two producers, a SIMD each; three
+// buffers of 40 x 65 16-byte entries are 122 KB of its CU's LDS.
+// 9,500 chunks of 256 KiB, with the reductions above them: 6.66 ms (3.2 us and
+// 1565 instructions per block) against 9.39 with one lane per chunk and one
+// producer (2163 instructions).
+//
+// Up to 128 chunks per CU: the two-pair kernel, one lane per chunk.  A
+// producer wave loads each block one block ahead, builds its 16 message words
+// (padding of FIPS 180-4 section 5.1.2: tail, 0x80, zeros, 128-bit bit length)
+// and expands them to the 80 schedule words (section 6.4 step 1) in a
+// double-buffered LDS area; a consumer wave runs only the 80 rounds and the
+// feed-forward.  Two pairs' schedules, 80 x 8 bytes per lane and buffer, fill
+// the CU's 160 KB of LDS.
+//
+// Synchronisation and exec mask: the chain kernel's barriers are those of the
+// SHA-256 one; both waves of a pair of the two-pair kernel run one barrier per
+// block (the workgroup's most blocks).  Barriers order LDS only.  Every lane
+// runs every block (dead lanes and finished chunks on zeros or stale words)
+// and only the loads, the state update and the digest store are per lane.
 #include "hv_kernels.h"
 #include "sha384_device.h"
 #include "split_common.h"
@@ -26,7 +43,8 @@
 namespace hv {
 namespace {
 
-constexpr int kGroups = 40;  // 80 schedule words, two per 16-byte LDS entry
+constexpr int kEntries = 40;  // 80 schedule words, two per 16-byte LDS entry
+constexpr int kRow = 65;       // a schedule row of the chain kernel: 64 chunks' entries, and the ones the a lanes add
 
 __device__ __forceinline__ uint32_t block_valid(uint32_t nfull, uint32_t r, uint32_t b) {
     return b < nfull ? 128u : (b == nfull ? r : 0u);
@@ -124,7 +142,7 @@ __device__ __forceinline__ void produce(uint32_t b, uint64_t src, uint64_t total
 template <bool kAligned>
 __device__ __forceinline__ void produce_all(uint64_t src, uint64_t total, uint32_t nfull, uint32_t r, uint32_t nblk,
                                             uint32_t nmax, uint32_t nfull_min, uint32_t lane,
-                                            uint4 (*sched)[kGroups][64]) {
+                                            uint4 (*sched)[kEntries][64]) {
     uint32_t A[33], B[33];
 #pragma unroll
     for (int k = 0; k < 33; ++k) A[k] = B[k] = 0;
@@ -135,16 +153,14 @@ __device__ __forceinline__ void produce_all(uint64_t src, uint64_t total, uint32
     }
 }
 
-template <int kPairs>
-__global__ void __launch_bounds__(128 * kPairs) sha384_split_kernel(const LeafDesc* __restrict__ desc,
-                                                                    uint64_t n_slots, uint64_t out_bound,
-                                                                    uint8_t* __restrict__ digests) {
+__global__ void __launch_bounds__(256) sha384_pairs_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                           uint64_t out_bound, uint8_t* __restrict__ digests) {
     // [pair][buffer][entry of two words][lane]
-    __shared__ uint4 sched[kPairs][2][kGroups][64];
+    __shared__ uint4 sched[2][2][kEntries][64];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t pair = wave >> 1;
-    const uint64_t base = (uint64_t)blockIdx.x * (64 * kPairs);
+    const uint64_t base = (uint64_t)blockIdx.x * 128;
     const uint64_t slot = base + 64 * pair + lane;
     const bool live = slot < n_slots;
     LeafDesc d = {0, 0, 0};
@@ -156,7 +172,7 @@ __global__ void __launch_bounds__(128 * kPairs) sha384_split_kernel(const LeafDe
     // blocks of any of its chunks
     uint32_t nmax = nblk;
     const uint64_t other = base + 64 * (pair ^ 1) + lane;
-    if (kPairs == 2 && other < n_slots) {
+    if (other < n_slots) {
         const uint64_t ob = desc[other].nbytes;
         const uint32_t on = (uint32_t)(ob >> 7) + ((ob & 127) <= 111 ? 1u : 2u);
         nmax = on > nmax ? on : nmax;
@@ -197,8 +213,8 @@ __global__ void __launch_bounds__(128 * kPairs) sha384_split_kernel(const LeafDe
 #pragma unroll
             for (int e = 0; e < 8; ++e) q[0][e] = buf[e][lane];
 #pragma unroll
-            for (int j = 0; j < kGroups / 8; ++j) {
-                if (j + 1 < kGroups / 8) {
+            for (int j = 0; j < kEntries / 8; ++j) {
+                if (j + 1 < kEntries / 8) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) q[(j + 1) & 1][e] = buf[8 * (j + 1) + e][lane];
                 }
@@ -223,6 +239,244 @@ __global__ void __launch_bounds__(128 * kPairs) sha384_split_kernel(const LeafDe
     }
 }
 
+// Producer p's blocks b = p, p + 2, ... of the chain kernel: as produce_all,
+// but each word with its round constant, into buffer b % 3, three fifths of a
+// block before barrier b and the rest before barrier b + 1.  Every producer
+// passes barriers 0..nmax.
+template <bool kAligned>
+__device__ __forceinline__ void produce_alternate(uint32_t p, uint64_t src, uint64_t total, uint32_t nfull, uint32_t r,
+                                                  uint32_t nblk, uint32_t nmax, uint32_t nfull_min, uint32_t lane,
+                                                  uint4 (*sched)[kEntries][kRow]) {
+    const uint32_t sh = kAligned ? 0u : (uint32_t)(src & 3);
+    uint32_t D[2][33];
+#pragma unroll
+    for (int k = 0; k < 33; ++k) D[0][k] = D[1][k] = 0;
+    if (p < nblk) load_block<kAligned>(src, block_valid(nfull, r, p), p, D[0]);
+    uint32_t passed = 0;  // barriers
+    if (p == 1) {
+        lds_barrier();
+        ++passed;
+    }
+    uint32_t slot = p;  // b % 3
+    for (uint32_t b0 = p; b0 < nmax; b0 += 4) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const uint32_t b = b0 + 2 * half;
+            if (b < nmax) {
+                uint32_t(&cur)[33] = D[half];
+                uint32_t(&nxt)[33] = D[half ^ 1];
+                wait_vmem();  // `cur` has landed; the loads below stay in flight
+                if (b + 2 < nblk) load_block<kAligned>(src, block_valid(nfull, r, b + 2), b + 2, nxt);
+                uint64_t W[16];
+                if (b < nfull_min)
+                    whole_block_words(cur, sh, W);
+                else
+                    block_words(cur, sh, total, nfull, r, b, W);
+                uint4(*buf)[kRow] = sched[slot];
+                slot = slot == 0 ? 2 : slot - 1;  // (b + 2) % 3
+#pragma unroll
+                for (int g = 0; g < 8; ++g)
+                    buf[g][lane] = entry(W[2 * g] + kRound512[2 * g], W[2 * g + 1] + kRound512[2 * g + 1]);
+#pragma nounroll
+                for (int trip = 1; trip < 5; ++trip) {
+                    if (trip == 3) lds_barrier();  // barrier b
+                    const uint64_t* k = kRound512 + 16 * trip;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        W[i] = small_sigma1_512(W[(i + 14) & 15]) + W[(i + 9) & 15] +
+                               small_sigma0_512(W[(i + 1) & 15]) + W[i];
+#pragma unroll
+                    for (int g = 0; g < 8; ++g)
+                        buf[8 * trip + g][lane] = entry(W[2 * g] + k[2 * g], W[2 * g + 1] + k[2 * g + 1]);
+                }
+                lds_barrier();  // barrier b + 1: block b's words are in buf
+                passed += 2;
+            }
+        }
+    }
+    for (; passed < nmax + 1; ++passed) lds_barrier();
+}
+
+// What tells the two lanes of a chunk apart.
+struct Half {
+    uint32_t r1, r2, r3;  // the lane's rotations: rotr(x ^ rotr(x, r1) ^ rotr(x, r2), r3) is its Sigma
+    uint32_t m;           // ~0 in a lanes, 0 in e lanes
+};
+
+__device__ __forceinline__ uint64_t rotr64_below_32(uint64_t x, uint32_t n) {
+    return pack(__builtin_amdgcn_alignbit(lo32(x), hi32(x), n), __builtin_amdgcn_alignbit(hi32(x), lo32(x), n));
+}
+
+// x plus the chunk's other lane's y.  A DPP operand may be read no sooner than
+// two instructions after it is written, and the compiler does not see into the
+// block: `after`, a value computed from y by several instructions, keeps it
+// that far behind, and where there is none (`fresh`) the block waits itself.
+template <bool fresh>
+__device__ __forceinline__ uint64_t add_partner(uint64_t x, uint64_t y, uint64_t after) {
+    uint32_t lo, hi;
+    if constexpr (fresh)
+        asm("s_nop 1\n\t"
+            "v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+            "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+            : "=&v"(lo), "=v"(hi) : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)) : "vcc");
+    else
+        asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+            "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+            : "=&v"(lo), "=v"(hi)
+            : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)), "v"(lo32(after))
+            : "vcc");
+    return pack(hi, lo);
+}
+
+// Step s of the lanes' shared recurrence: R[(i - s) & 3] is the lane's value i
+// steps old, and the new value takes the oldest one's place.  Four instructions
+// depend on each other from one step to the next (a dependent one issues 8
+// cycles later): the partner's value joins h + K + W, off that path.
+template <int s>
+__device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t kw) {
+    const uint64_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3], x3 = R[(3 - s) & 3];
+    const uint64_t m = pack(c.m, c.m);
+    const uint64_t sigma = rotr64_below_32(bitop3_64<0x96>(x0, rotr64_below_32(x0, c.r1), rotr64_below_32(x0, c.r2)),
+                                           c.r3);
+    const uint64_t p = bitop3_64<0x2D>(x0, x1, m);   // a ^ b, or ~e
+    const uint64_t f = bitop3_64<0xCA>(p, x2, x1);   // Maj(a, b, c), or Ch(e, f, g)
+    const uint64_t q = pack(hi32(x3) ^ c.m, lo32(x3) ^ c.m) + kw;  // -d, or h + K + W
+    R[(3 - s) & 3] = sigma + (f + add_partner<s == 0>(q, x1, x0));
+}
+
+template <int s, int end>
+__device__ __forceinline__ void steps(uint64_t R[4], const uint64_t H[4], const Half& c, const uint4 q[8]) {
+    if constexpr (s < end) {
+        const uint4 w = q[(s >> 1) & 7];
+        step<s>(R, c, s & 1 ? pack(w.w, w.z) : pack(w.y, w.x));
+        // the a lanes' first two values are the block's b and a themselves
+        if (s == 0) R[3] = c.m ? H[3] : R[3];
+        if (s == 1) R[2] = c.m ? H[2] : R[2];
+        steps<s + 1, end>(R, H, c, q);
+    }
+}
+
+// A consumer's work for block b: 80 steps of the e lanes with the a lanes two
+// steps behind, the words in five groups of 16.  `cur` is being read on entry;
+// group j + 1's reads (after group 4 those of block b + 1, past its barrier)
+// are issued before group j's steps, which the scheduling barrier keeps there,
+// and land under them.  H holds (H4, H5, H6, H7) in e lanes and (H2, H3, H0,
+// H1) in a lanes; slot: b % 3, moved on.
+__device__ __forceinline__ void consume(uint32_t b, uint32_t& slot, uint32_t nmax, uint32_t nblk, uint32_t col,
+                                        uint4 (*sched)[kEntries][kRow], uint64_t H[4], const Half& c, uint4 cur[8],
+                                        uint4 nxt[8]) {
+    uint64_t R[4] = {H[0], H[1], H[2], H[3]};
+    auto read = [&](uint32_t from, int j, uint4 q[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = sched[from][8 * j + e][col];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    wait_lds();
+    read(slot, 1, nxt);
+    steps<0, 16>(R, H, c, cur);
+    wait_lds();
+    read(slot, 2, cur);
+    steps<16, 32>(R, H, c, nxt);
+    wait_lds();
+    read(slot, 3, nxt);
+    steps<32, 48>(R, H, c, cur);
+    wait_lds();
+    read(slot, 4, cur);
+    steps<48, 64>(R, H, c, nxt);
+    wait_lds();
+    slot = slot == 2 ? 0 : slot + 1;
+    if (b + 1 < nmax) {
+        lds_barrier();  // barrier b + 2: block b + 1's words are in its buffer
+        read(slot, 0, nxt);
+    }
+    steps<64, 80>(R, H, c, cur);
+    uint64_t at80[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at80[i] = R[i];
+    step<80>(R, c, 1);
+    step<81>(R, c, 1);
+    if (b < nblk) {
+        H[0] += at80[0];
+        H[1] += at80[1];
+        H[2] += c.m ? R[2] : at80[2];
+        H[3] += c.m ? R[3] : at80[3];
+    }
+}
+
+__global__ void __launch_bounds__(256) sha384_chain_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                           uint64_t out_bound, uint8_t* __restrict__ digests) {
+    __shared__ uint4 sched[3][kEntries][kRow];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t base = (uint64_t)blockIdx.x * 64;
+    // every wave holds the 64 descriptors once, for the block counts
+    uint64_t slot = base + lane;
+    bool live = slot < n_slots;
+    LeafDesc d = {0, 0, 0};
+    if (live) d = desc[slot];
+    uint32_t nfull = (uint32_t)(d.nbytes >> 7), r = (uint32_t)(d.nbytes & 127);
+    uint32_t nblk = live ? nfull + (r <= 111 ? 1u : 2u) : 0u;
+    uint32_t nmax = nblk, nfull_min = live ? nfull : 0xffffffffu;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(nfull_min, o);
+        nmax = x > nmax ? x : nmax;
+        nfull_min = y < nfull_min ? y : nfull_min;
+    }
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    nfull_min = __builtin_amdgcn_readfirstlane(nfull_min);
+
+    if (wave >= 2) {
+        const uint32_t p = wave & 1;
+        // the ones, each producer's half of them before barrier 1
+        if (lane < 60) sched[(60 * p + lane) / kEntries][(60 * p + lane) % kEntries][64] = make_uint4(1, 0, 1, 0);
+        if (__all((d.src & 15) == 0))
+            produce_alternate<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched);
+        else
+            produce_alternate<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched);
+        return;
+    }
+    const uint32_t chunk = 32 * wave + (lane >> 1);
+    slot = base + chunk;
+    live = slot < n_slots;
+    d = {0, 0, 0};
+    if (live) d = desc[slot];
+    nfull = (uint32_t)(d.nbytes >> 7);
+    r = (uint32_t)(d.nbytes & 127);
+    nblk = live ? nfull + (r <= 111 ? 1u : 2u) : 0u;
+    const bool e = lane & 1;
+    const Half c = {e ? 4u : 6u, e ? 27u : 11u, e ? 14u : 28u, e ? 0u : ~0u};
+    uint64_t H[4] = {e ? kInit384[4] : kInit384[2], e ? kInit384[5] : kInit384[3], e ? kInit384[6] : kInit384[0],
+                     e ? kInit384[7] : kInit384[1]};
+    const uint32_t col = e ? chunk : 64u;
+    uint4 A[8], B[8];  // five groups per block: the sets' roles swap from block to block
+    if (nmax > 0) {
+        lds_barrier();
+        lds_barrier();  // block 0's words are in buffer 0
+#pragma unroll
+        for (int g = 0; g < 8; ++g) A[g] = sched[0][g][col];
+    }
+    uint32_t buf = 0;  // b % 3
+    for (uint32_t b = 0; b < nmax; b += 2) {
+        consume(b, buf, nmax, nblk, col, sched, H, c, A, B);
+        if (b + 1 < nmax) consume(b + 1, buf, nmax, nblk, col, sched, H, c, B, A);
+    }
+    if (live && d.out < out_bound) {
+        // H0..H3 from the a lane, H4 and H5 from the e lane
+        uint4* out = reinterpret_cast<uint4*>(digests + 48 * d.out);
+        const uint4 first = make_uint4(__builtin_bswap32(hi32(H[0])), __builtin_bswap32(lo32(H[0])),
+                                       __builtin_bswap32(hi32(H[1])), __builtin_bswap32(lo32(H[1])));
+        const uint4 second = make_uint4(__builtin_bswap32(hi32(H[2])), __builtin_bswap32(lo32(H[2])),
+                                        __builtin_bswap32(hi32(H[3])), __builtin_bswap32(lo32(H[3])));
+        if (e) {
+            out[2] = first;
+        } else {
+            out[0] = second;
+            out[1] = first;
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_sha384_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
@@ -237,9 +491,9 @@ hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t 
     for (uint64_t base = 0; base < n_slots; base += kMaxSlotsPerLaunch) {
         const uint64_t n = n_slots - base < kMaxSlotsPerLaunch ? n_slots - base : kMaxSlotsPerLaunch;
         if (!two_pairs)
-            sha384_split_kernel<1><<<(unsigned)((n + 63) / 64), 128, 0, s>>>(desc + base, n, out_bound, digests);
+            sha384_chain_kernel<<<(unsigned)((n + 63) / 64), 256, 0, s>>>(desc + base, n, out_bound, digests);
         else
-            sha384_split_kernel<2><<<(unsigned)((n + 127) / 128), 256, 0, s>>>(desc + base, n, out_bound, digests);
+            sha384_pairs_kernel<<<(unsigned)((n + 127) / 128), 256, 0, s>>>(desc + base, n, out_bound, digests);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

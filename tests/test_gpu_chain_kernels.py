@@ -1,0 +1,48 @@
+"""The two-lane chain kernels at their edges against the CPU oracle: chunk
+counts around a consumer wave (32) and a group (64), block counts around the
+three schedule buffers and the two alternate producers, chunks that end blocks
+before their neighbours, and every start within a 16-byte granule.  Digests are
+compared exactly."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import oracle
+
+from paper_2510_23938_amd import hv
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda")
+BLOCK = {"sha256": 64, "sha384": 128}
+
+
+def run_lengths(lens, align, alg, seed):
+    """Leaf digests of whole messages of these lengths, message i starting ``align`` * i mod 16 past a granule."""
+    starts, pos = [], 0
+    for i, n in enumerate(lens):
+        starts.append(pos + align * i % 16)
+        pos = (starts[-1] + n + 31) // 16 * 16
+    buf = W.random_bytes(pos + 16, seed, DEV)
+    ptrs = np.uint64(buf.data_ptr()) + np.array(starts, dtype=np.uint64)
+    leaves, _ = hv.hv_hash_chunks((ptrs, np.array(lens, dtype=np.uint64)), 0, alg=alg)
+    host = buf.cpu().numpy()
+    want = oracle.leaf_digests_mt([host[s:s + n].tobytes() for s, n in zip(starts, lens)], 0, 4, alg)
+    return leaves.cpu().numpy(), want
+
+
+@pytest.mark.parametrize("alg", ["sha256", "sha384"])
+@pytest.mark.parametrize("align", [0, 1])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 127, 129])
+def test_edges(n, align, alg):
+    hv.set_leaf_kernel("two-wave")
+    try:
+        for blocks in range(1, 9):  # the group's most blocks, padding included
+            top = blocks * BLOCK[alg] - (9 if alg == "sha256" else 17)
+            rng = np.random.default_rng([n, blocks])
+            lens = rng.integers(0, top, n, endpoint=True)
+            lens[rng.integers(0, n)] = top
+            got, want = run_lengths([int(x) for x in lens], align, alg, 900 + blocks)
+            assert np.array_equal(got, want), f"{blocks} blocks"
+    finally:
+        hv.set_leaf_kernel("auto")
