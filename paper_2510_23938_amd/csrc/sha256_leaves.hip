@@ -134,8 +134,9 @@ __device__ __forceinline__ void gather_words(const uint8_t* p, uint32_t valid, u
     const uint32_t sh = (uint32_t)(pa & 3);
     const uint32_t* a = reinterpret_cast<const uint32_t*>(pa - sh);
     uint32_t D[17];
+    const uint32_t end = valid > 0 ? sh + valid : 0u;  // no bytes: no loads, whatever the address
 #pragma unroll
-    for (int k = 0; k < 17; ++k) D[k] = (uint32_t)(4 * k) < sh + valid ? a[k] : 0u;
+    for (int k = 0; k < 17; ++k) D[k] = (uint32_t)(4 * k) < end ? a[k] : 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) X[i] = __builtin_amdgcn_alignbyte(D[i + 1], D[i], sh);
 }

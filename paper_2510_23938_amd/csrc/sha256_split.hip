@@ -93,8 +93,9 @@ __device__ __forceinline__ void load_block(uint64_t src, uint32_t valid, uint32_
     } else {
         const uint32_t sh = (uint32_t)(src & 3);
         const gwords w = reinterpret_cast<gwords>(src + 64 * (uint64_t)b - sh);
+        const uint32_t end = valid > 0 ? sh + valid : 0u;  // no bytes: no loads, whatever the address
 #pragma unroll
-        for (int k = 0; k < 17; ++k) D[k] = (uint32_t)(4 * k) < sh + valid ? w[k] : 0u;
+        for (int k = 0; k < 17; ++k) D[k] = (uint32_t)(4 * k) < end ? w[k] : 0u;
     }
 }
 

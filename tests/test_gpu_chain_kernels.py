@@ -46,3 +46,17 @@ def test_edges(n, align, alg):
             assert np.array_equal(got, want), f"{blocks} blocks"
     finally:
         hv.set_leaf_kernel("auto")
+
+
+@pytest.mark.parametrize("alg", ["sha256", "sha384"])
+@pytest.mark.parametrize("choice", ["one-wave", "two-wave", "two-wave-compact"])
+def test_no_bytes_at_odd_addresses(choice, alg):
+    # blocks that hold none of a chunk's bytes (an empty message's, and the
+    # length-only one after a long tail) are formed without loads
+    hv.set_leaf_kernel(choice)
+    try:
+        tail = BLOCK[alg] - 1
+        got, want = run_lengths([0, tail, 0, BLOCK[alg] + tail, BLOCK[alg], 0, 1], 5, alg, 31)
+        assert np.array_equal(got, want)
+    finally:
+        hv.set_leaf_kernel("auto")
