@@ -694,7 +694,7 @@ def main():
     achieved = blocks * ops_per_block / (k_ms / 1e3) / 1e12
     ran = hv.leaf_kernel_for(pipe.n_leaves)  # the leaf kernel the timed passes ran
     if ran != "one-wave":
-        leaf_kernel = f"{alg}_split_kernel"
+        leaf_kernel = "sha384_pairs_kernel" if (alg, ran) == ("sha384", "two-wave-compact") else f"{alg}_chain_kernel"
     log(f"{args.steps} steps: {ms_step:.2f} ms/step, {value:.1f} GB/s (median step {med:.2f} ms, spread "
         f"{step_stats['spread_pct']:.2f}%); leaf kernel {k_ms:.2f} ms avg ({total / k_ms / 1e6:.1f} GB/s, "
         f"{achieved:.2f} TOP/s); prepared pass {prepared_ms:.2f} ms/step")

@@ -34,15 +34,18 @@ hv_status hv_leaf_schedule(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_b
  * two lanes) and shortens each chunk's chain of blocks; others use the
  * one-wave kernel), 1 = always the one-wave kernel, 2 = always the two-wave
  * kernel, 3 = always the two-wave kernel with twice the chunks, 128, per
- * workgroup (the layout it takes above 64 leaves per compute unit).  Monitor scans (hv_monitor.h) take the
+ * workgroup (the layout it takes above 64 leaves per compute unit).  From 128 to
+ * 192 leaves per compute unit the automatic choice runs SHA-256's three-group
+ * kernel (one lane per chunk, the schedules on other waves) in the one-wave
+ * kernel's place.  Monitor scans (hv_monitor.h) take the
  * one-wave kernel under the automatic choice.  The same choice applies to
  * SHA-384's two leaf kernels.  The digests do not depend on it.
  * Errors: HV_ERR_INVALID_ARG for another value. */
 hv_status hv_set_leaf_kernel(int choice);
 
 /* The leaf kernel a hash call over n_leaves leaves would run on the current
- * device under this thread's choice: *kernel = 1 (one-wave), 2 (two-wave, 64
- * chunks per workgroup) or 3 (two-wave, 128).  Monitor
+ * device under this thread's choice: *kernel = 1 (one-wave, or three-group as
+ * above), 2 (two-wave, 64 chunks per workgroup) or 3 (two-wave, 128).  Monitor
  * scans take the one-wave kernel under the automatic choice.
  * Errors: HV_ERR_INVALID_ARG for a NULL kernel. */
 hv_status hv_leaf_kernel_for(uint64_t n_leaves, int* kernel);

@@ -74,6 +74,11 @@ __device__ __forceinline__ uint32_t block_valid(uint32_t nfull, uint32_t r, uint
     return b < nfull ? 64u : (b == nfull ? r : 0u);
 }
 
+// The same from the chunk's byte count alone: 0 past its last byte.
+__device__ __forceinline__ uint32_t valid_of(uint64_t nbytes, uint32_t b) {
+    return block_valid((uint32_t)(nbytes >> 6), (uint32_t)(nbytes & 63), b);
+}
+
 // Block b's bytes into D.  kAligned (the chunk starts on a 16-byte boundary):
 // the 16-byte granules that hold chunk bytes, with four 16-byte loads, into
 // D[0..15] (D[16] is left as it is: with sh = 0 it does not enter the words).
@@ -333,6 +338,205 @@ __global__ void __launch_bounds__(256 * kGroups) sha256_chain_kernel(const LeafD
     }
 }
 
+// ---------------------------------------------------------------------------
+// Three groups of 64 chunks per CU, one lane per chunk, for calls between 128
+// and 192 chunks per CU.  A block's rounds are 903 instructions on its
+// consumer and its words about 530 on a producer, so three groups are 1080 per
+// SIMD if they are spread evenly.  A SIMD each for the consumers (waves 0-2)
+// leaves the fourth to two producers (waves 3 and 7), which make two of the
+// three groups' blocks; the third's comes from a helper on the SIMD of its
+// consumer (waves 4-6), every third block, over three block times.  The two
+// producers run at 4.8 cycles per instruction and the other SIMDs at 4.1, so
+// the consumers make the last four words themselves: 36,800 chunks of 64 KiB
+// take 2.29 ms without that, 2.13 with four words and 2.16 with eight (their
+// own values are at hand, and nothing is sent).  Of two waves on a SIMD the
+// older is issued first, and the younger producer then runs the second half
+// of its block alone, at a lone wave's rate: with priority for the first 12 of
+// its 15 entries 2.07 ms.  The one-wave kernel, a wave alone on each SIMD with
+// 1405 instructions per block, takes 2.72.
+//
+// Interval u ends with barrier u.  Block b of a group is complete at barrier b
+// (a producer's in interval b, a helper's, b % 3 == g, in b - 2 to b), is read
+// into registers in interval b + 1 and run after barrier b + 1.  So a
+// producer's buffer is busy for two intervals and a helper's for four, and
+// three per group are enough (triple_buffer).
+
+constexpr int kTriple = 3;
+constexpr int kSent = 15;  // entries of four words a producer makes
+constexpr int kAhead = 12;  // of these the younger producer makes with priority
+
+// The schedule buffer of group g's block b: with k the count of the group's
+// helper blocks before, they take buffers k % 3; a block after such a one
+// takes (k + 2) % 3 and the next k % 3, free again by then.
+__device__ __forceinline__ uint32_t triple_buffer(uint32_t b, uint32_t g) {
+    const uint32_t k = (b + 9 - g) / 3, r = b + 9 - g - 3 * k;
+    return (r == 1 ? k + 2 : k) % 3;
+}
+
+struct TripleLds {
+    uint4 sched[kTriple][3][kSent][64];
+    uint64_t src[kTriple][64], nbytes[kTriple][64];
+};
+
+// A producer's blocks b = first, first + stride, ..., block b for group g,
+// which moves on by `turn` groups from block to block.  `younger`: wave 7.
+template <bool kAligned>
+__device__ __forceinline__ void triple_produce(uint32_t first, uint32_t stride, uint32_t g, uint32_t turn,
+                                               bool younger, uint32_t nmax, uint32_t lane, TripleLds& lds) {
+    uint32_t D[2][17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) D[0][k] = D[1][k] = 0;
+    uint64_t src = lds.src[g][lane], total = lds.nbytes[g][lane];
+    if (first < nmax) load_block<kAligned>(src, valid_of(total, first), first, D[0]);
+    uint32_t passed = 0;  // barriers
+    for (uint32_t b0 = first; b0 < nmax; b0 += 2 * stride) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const uint32_t b = b0 + half * stride;
+            if (b < nmax) {
+                if (younger) __builtin_amdgcn_s_setprio(1);
+                const uint32_t after = g + turn < kTriple ? g + turn : g + turn - kTriple;
+                const uint64_t src1 = lds.src[after][lane], total1 = lds.nbytes[after][lane];
+                uint32_t(&cur)[17] = D[half];
+                wait_vmem();  // `cur` has landed; the loads below stay in flight
+                load_block<kAligned>(src1, valid_of(total1, b + stride), b + stride, D[half ^ 1]);
+                const uint32_t sh = kAligned ? 0u : (uint32_t)(src & 3);
+                const uint32_t nfull = (uint32_t)(total >> 6), r = (uint32_t)(total & 63);
+                uint32_t W[16];
+                if (__any(b - nfull < (r <= 55 ? 1u : 2u)))  // padding in this block of some chunk
+                    block_words(cur, sh, total, nfull, r, b, W);
+                else
+                    whole_block_words(cur, sh, W);
+                uint4(*buf)[64] = lds.sched[g][triple_buffer(b, g)];
+#pragma unroll
+                for (int q = 0; q < kSent; ++q) {
+#pragma unroll
+                    for (int t = 4 * q; t < 4 * q + 4; ++t)
+                        if (t >= 16)
+                            W[t & 15] = small_sigma1(W[(t - 2) & 15]) + W[(t - 7) & 15] +
+                                        small_sigma0(W[(t - 15) & 15]) + W[t & 15];
+                    buf[q][lane] = make_uint4(W[(4 * q) & 15], W[(4 * q + 1) & 15], W[(4 * q + 2) & 15],
+                                              W[(4 * q + 3) & 15]);
+                    if (younger && q == kAhead - 1) __builtin_amdgcn_s_setprio(0);
+                    // a helper's thirds of a block
+                    if ((q == 6 && passed + 1 < b) || (q == 10 && passed < b)) {
+                        lds_barrier();
+                        ++passed;
+                    }
+                }
+                lds_barrier();  // barrier b
+                ++passed;
+                src = src1;
+                total = total1;
+                g = after;
+            }
+        }
+    }
+    for (; passed < nmax; ++passed) lds_barrier();
+}
+
+__device__ __forceinline__ void triple_consume(uint32_t b, uint32_t g, uint32_t nmax, uint32_t nblk, uint32_t lane,
+                                               TripleLds& lds, uint32_t H[8], const uint4 cur[kSent], uint4 nxt[kSent]) {
+    wait_lds();  // `cur` has landed; here, so that no wait for it also waits for the reads below
+    if (b + 1 < nmax) {
+        lds_barrier();  // barrier b + 1
+        uint4(*buf)[64] = lds.sched[g][triple_buffer(b + 1, g)];
+#pragma unroll
+        for (int q = 0; q < kSent; ++q) nxt[q] = buf[q][lane];
+    }
+    uint32_t s[8], W[64];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = H[i];
+#pragma unroll
+    for (int q = 0; q < kSent; ++q) {
+        W[4 * q] = cur[q].x; W[4 * q + 1] = cur[q].y; W[4 * q + 2] = cur[q].z; W[4 * q + 3] = cur[q].w;
+    }
+#pragma unroll
+    for (int t = 0; t < 64; ++t) {
+        if (t >= 4 * kSent) W[t] = small_sigma1(W[t - 2]) + W[t - 7] + small_sigma0(W[t - 15]) + W[t - 16];
+        const uint32_t w = W[t];
+        const uint32_t e = s[(12 - t) & 7], a = s[(8 - t) & 7];
+        const uint32_t t1 = s[(15 - t) & 7] + kRound[t] + w + big_sigma1(e) +
+                            choose(e, s[(13 - t) & 7], s[(14 - t) & 7]);
+        const uint32_t t2 = big_sigma0(a) + majority(a, s[(9 - t) & 7], s[(10 - t) & 7]);
+        s[(11 - t) & 7] += t1;
+        s[(15 - t) & 7] = t1 + t2;
+    }
+    // a select: under a branch the compiler would move the rounds there too
+    const uint32_t on = b < nblk ? ~0u : 0u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) H[i] += s[i] & on;
+}
+
+__global__ void __launch_bounds__(512) sha256_triple_kernel(const LeafDesc* __restrict__ desc, uint64_t n_slots,
+                                                            uint64_t out_bound, uint8_t* __restrict__ digests) {
+    __shared__ TripleLds lds;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t base = (uint64_t)blockIdx.x * (64 * kTriple);
+    // every wave counts the workgroup's blocks
+    uint32_t nmax = 0;
+    bool aligned = true;
+#pragma unroll
+    for (int g = 0; g < kTriple; ++g) {
+        const uint64_t slot = base + 64 * g + lane;
+        LeafDesc d = {0, 0, 0};
+        if (slot < n_slots) {
+            d = desc[slot];
+            const uint32_t nfull = (uint32_t)(d.nbytes >> 6);
+            const uint32_t nblk = nfull + ((d.nbytes & 63) <= 55 ? 1u : 2u);
+            nmax = nblk > nmax ? nblk : nmax;
+            aligned = aligned && (d.src & 15) == 0;
+        }
+        if (wave == g) {
+            lds.src[g][lane] = d.src;
+            lds.nbytes[g][lane] = d.nbytes;
+        }
+    }
+    aligned = __all(aligned);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t x = __shfl_xor(nmax, o);
+        nmax = x > nmax ? x : nmax;
+    }
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    lds_barrier();  // the descriptors are in LDS
+
+    if (wave >= kTriple) {
+        const bool helper = wave != 3 && wave != 7;
+        // block 0: waves 3 and 7 make groups 1 and 2, the helper of group 0 the other
+        const uint32_t g = wave == 3 ? 1u : wave == 7 ? 2u : wave - 4;
+        const uint32_t first = helper ? g : 0u, stride = helper ? 3u : 1u, turn = helper ? 0u : 1u;
+        if (aligned)
+            triple_produce<true>(first, stride, g, turn, wave == 7, nmax, lane, lds);
+        else
+            triple_produce<false>(first, stride, g, turn, wave == 7, nmax, lane, lds);
+        return;
+    }
+    const uint64_t slot = base + 64 * wave + lane;
+    const bool live = slot < n_slots;
+    const uint64_t total = lds.nbytes[wave][lane];
+    const uint32_t nblk = live ? (uint32_t)(total >> 6) + ((total & 63) <= 55 ? 1u : 2u) : 0u;
+    __builtin_amdgcn_s_setprio(2);  // over the helper's, whose thirds are due no sooner
+    uint32_t H[8];
+    init_state(H);
+    uint4 A[kSent], B[kSent];
+    if (nmax > 0) {
+        lds_barrier();  // barrier 0
+        uint4(*buf)[64] = lds.sched[wave][triple_buffer(0, wave)];
+#pragma unroll
+        for (int q = 0; q < kSent; ++q) A[q] = buf[q][lane];
+    }
+    for (uint32_t b = 0; b < nmax; b += 2) {
+        triple_consume(b, wave, nmax, nblk, lane, lds, H, A, B);
+        if (b + 1 < nmax) triple_consume(b + 1, wave, nmax, nblk, lane, lds, H, B, A);
+    }
+    if (live) {
+        const uint64_t out = desc[slot].out;
+        if (out < out_bound) store_digest(digests + 32 * out, H);
+    }
+}
+
 }  // namespace
 
 // Compute units of the current device, queried once per device.
@@ -354,7 +558,8 @@ int leaf_kernel_for(uint64_t n_slots, bool background) {
     // the two-wave kernels while every CU holds one workgroup at most: 64
     // KiB chunks take 1.31 ms up to 64 per CU and 1.70 up to 128, against 2.69
     // with the one-wave kernel; with more, two workgroups share a CU and the
-    // one-wave kernel is faster.  Background work keeps the one-wave kernel:
+    // one-wave kernel (or SHA-256's three-group one, launch_sha256_auto) is
+    // faster.  Background work keeps the one-wave kernel:
     // shorter chains cost more instructions, about 1.4x the CU time per byte.
     if (choice == 1 || (choice == 0 && (background || n_slots > 128 * cus))) return 1;
     return choice == 3 || n_slots > 64 * cus ? 3 : 2;
@@ -384,7 +589,17 @@ uint32_t tape_waves(uint64_t n_slots) {
 hipError_t launch_sha256_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background) {
     const int k = leaf_kernel_for(n_slots, background);
-    if (k == 1) return launch_sha256_leaves(desc, n_slots, out_bound, digests, s);
+    if (k == 1) {
+        // up to three groups per CU, one workgroup each: 2.07 ms against 2.72
+        // for 64 KiB chunks (above kSent); with more, the one-wave kernel has a
+        // wave for every SIMD.  Background work as above.
+        if (leaf_kernel_choice() == 0 && !background && n_slots <= 64 * kTriple * (uint64_t)device_cus()) {
+            sha256_triple_kernel<<<(unsigned)((n_slots + 64 * kTriple - 1) / (64 * kTriple)), 512, 0, s>>>(
+                desc, n_slots, out_bound, digests);
+            return hipGetLastError();
+        }
+        return launch_sha256_leaves(desc, n_slots, out_bound, digests, s);
+    }
     return launch_sha256_split(desc, n_slots, out_bound, digests, k == 3, s);
 }
 

@@ -60,3 +60,18 @@ def test_no_bytes_at_odd_addresses(choice, alg):
         assert np.array_equal(got, want)
     finally:
         hv.set_leaf_kernel("auto")
+
+
+@pytest.mark.parametrize("align", [0, 1])
+@pytest.mark.parametrize("per_cu", [128, 150, 192])
+def test_three_groups_per_cu(per_cu, align):
+    # above 128 and up to 192 chunks per CU: workgroups (the table is sorted by
+    # length) whose longest chunk has 1 to 12 blocks and one of 70, the last
+    # workgroup partly filled
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = per_cu * cus + (1 if per_cu == 128 else 0)
+    rng = np.random.default_rng([per_cu, align])
+    lens = rng.integers(0, 12 * 64 - 9, n, endpoint=True)
+    lens[rng.integers(0, n, 5)] = 70 * 64 - 9
+    got, want = run_lengths([int(x) for x in lens], align, "sha256", 950)
+    assert np.array_equal(got, want)
