@@ -385,6 +385,10 @@ hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64
 hv_status queue_schedule(const hv::MsgDesc* msgs_dev, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_full,
                          uint64_t n_leaves, const HashLayout& L, hipStream_t stream) {
     hipError_t e;
+    if (n_msgs > 0 && n_msgs <= hv::kSmallMessages) {
+        e = hv::launch_sched_small(msgs_dev, n_msgs, chunk_bytes, n_full, L.off, L.desc, stream);
+        return e == hipSuccess ? HV_OK : hip_fail(e, "schedule kernel");
+    }
     if ((e = hv::launch_sched_count(msgs_dev, n_msgs, chunk_bytes, L.cnt, stream)) != hipSuccess)
         return hip_fail(e, "count kernel");
     if ((e = hv::launch_scan_pairs(L.cnt, L.off, n_msgs, L.partials, stream)) != hipSuccess)

@@ -256,13 +256,18 @@ hv_status hv_rehash_chunks_alg(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, 
     if (e == hipSuccess)
         e = hipMemcpyWithStream(R.list, leaves, n_listed * sizeof(uint64_t), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_fail(e, "upload");
-    if ((e = hv::launch_sched_count(L.msgs, n_msgs, chunk_bytes, L.cnt, stream)) != hipSuccess)
-        return hip_fail(e, "count kernel");
-    if ((e = hv::launch_scan_pairs(L.cnt, L.off, n_msgs, L.partials, stream)) != hipSuccess)
-        return hip_fail(e, "scan kernels");
-    if ((e = hv::launch_sched_select(L.msgs, L.off, n_msgs, chunk_bytes, R.list, n_listed, L.desc, stream)) !=
-        hipSuccess)
-        return hip_fail(e, "select kernel");
+    if (n_msgs <= hv::kSmallMessages && n_leaves <= kMaxLeaves) {
+        e = hv::launch_select_small(L.msgs, n_msgs, chunk_bytes, R.list, n_listed, L.desc, stream);
+        if (e != hipSuccess) return hip_fail(e, "select kernel");
+    } else {
+        if ((e = hv::launch_sched_count(L.msgs, n_msgs, chunk_bytes, L.cnt, stream)) != hipSuccess)
+            return hip_fail(e, "count kernel");
+        if ((e = hv::launch_scan_pairs(L.cnt, L.off, n_msgs, L.partials, stream)) != hipSuccess)
+            return hip_fail(e, "scan kernels");
+        if ((e = hv::launch_sched_select(L.msgs, L.off, n_msgs, chunk_bytes, R.list, n_listed, L.desc, stream)) !=
+            hipSuccess)
+            return hip_fail(e, "select kernel");
+    }
     e = alg == HV_SHA384 ? hv::launch_sha384_auto(L.desc, n_listed, n_leaves, leaf_digests, stream)
                          : hv::launch_sha256_auto(L.desc, n_listed, n_leaves, leaf_digests, stream);
     if (e != hipSuccess) return hip_fail(e, "leaf kernel");

@@ -58,6 +58,15 @@ hipError_t launch_sched_full(const MsgDesc* msgs, const Pair* off, uint32_t n, u
 hipError_t launch_sched_tails(const MsgDesc* msgs, const Pair* off, uint32_t n, uint64_t C, uint64_t n_full,
                               uint64_t* hist, LeafDesc* desc, hipStream_t s);
 
+// The same table and offsets in one launch for up to kSmallMessages messages
+// (0 < n), and select's.  A one-shot call over 24 short tensors, hash to
+// verdict: 285 us with the nine launches, 243 with this one.
+constexpr uint32_t kSmallMessages = 1024;
+hipError_t launch_sched_small(const MsgDesc* msgs, uint32_t n, uint64_t C, uint64_t n_full, Pair* off, LeafDesc* desc,
+                              hipStream_t s);
+hipError_t launch_select_small(const MsgDesc* msgs, uint32_t n, uint64_t C, const uint64_t* leaves, uint64_t k,
+                               LeafDesc* desc, hipStream_t s);
+
 // Lays a scheduled leaf table (full chunks first, then tails by falling block
 // class) out as a tape for t.waves waves and clears t.ready; off[n_msgs].x is
 // the number of full chunks.

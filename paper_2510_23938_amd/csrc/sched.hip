@@ -322,6 +322,144 @@ __global__ void __launch_bounds__(kThreads) tape_plan_kernel(const LeafDesc* __r
     }
 }
 
+// Up to kSmallMessages messages: every workgroup counts and scans all of them
+// itself, one message per thread, so that a call's table takes one launch.
+// The launches above are nine for such a call, each a few microseconds long
+// and apart.
+struct SmallOffsets {
+    uint64_t data[kSmallMessages];
+    uint32_t full[kSmallMessages + 1];   // full chunks of the messages before
+    uint32_t tails[kSmallMessages + 1];  // their tails
+    uint64_t wave[kSmallMessages / 64];
+};
+
+// Fills `o` for messages 0..n - 1 (entry n: the totals, which fit 32 bits: a
+// call has at most 2^31 leaves); this thread's message, and its full chunks.
+__device__ __forceinline__ MsgDesc small_offsets(const MsgDesc* __restrict__ msgs, uint32_t n, uint64_t C,
+                                                 SmallOffsets& o, uint64_t* n_full) {
+    const uint32_t m = threadIdx.x, lane = m & 63;
+    MsgDesc msg = {0, 0};
+    uint64_t full = 0, own = 0;  // own: full chunks above, the tail below
+    if (m < n) {
+        msg = msgs[m];
+        full = C == 0 ? 0 : msg.nbytes / C;
+        own = full << 32 | (C == 0 || msg.nbytes != full * C ? 1u : 0u);
+    }
+    uint64_t sum = own;  // inclusive
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t below = __shfl_up(sum, d);
+        if (lane >= (uint32_t)d) sum += below;
+    }
+    if (lane == 63) o.wave[m >> 6] = sum;
+    o.data[m] = msg.data;
+    __syncthreads();
+    uint64_t before = 0;
+    for (uint32_t w = 0; w < m >> 6; ++w) before += o.wave[w];
+    sum += before - own;  // exclusive
+    if (m < n) {
+        o.full[m] = (uint32_t)(sum >> 32);
+        o.tails[m] = (uint32_t)sum;
+    }
+    if (m + 1 == n) {
+        o.full[n] = (uint32_t)((sum + own) >> 32);
+        o.tails[n] = (uint32_t)(sum + own);
+    }
+    __syncthreads();
+    *n_full = full;
+    return msg;
+}
+
+// The leaf table of such a call and its offsets: block 0 sorts the tails and
+// writes `off`, the others write the full chunks.
+__global__ void __launch_bounds__(kSmallMessages) schedule_small_kernel(const MsgDesc* __restrict__ msgs, uint32_t n,
+                                                                        uint64_t C, uint64_t n_full,
+                                                                        Pair* __restrict__ off,
+                                                                        LeafDesc* __restrict__ desc) {
+    __shared__ SmallOffsets o;
+    __shared__ uint32_t cursor[kSortBuckets];  // tails per class, then the class's next slot
+    __shared__ uint32_t wave_tails[kSmallMessages / 64];
+    const uint32_t m = threadIdx.x;
+    uint64_t full;
+    const MsgDesc msg = small_offsets(msgs, n, C, o, &full);
+    if (blockIdx.x > 0) {
+        for (uint64_t f = (uint64_t)(blockIdx.x - 1) * kSmallMessages + m; f < n_full;
+             f += (uint64_t)(gridDim.x - 1) * kSmallMessages) {
+            uint32_t lo = 0, hi = n;  // full[lo] <= f < full[hi]
+            while (hi - lo > 1) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if (o.full[mid] <= f) lo = mid; else hi = mid;
+            }
+            LeafDesc d;
+            d.src = o.data[lo] + (f - o.full[lo]) * C;
+            d.nbytes = C;
+            d.out = f + o.tails[lo];
+            desc[f] = d;
+        }
+        return;
+    }
+    for (uint32_t i = m; i <= n; i += kSmallMessages) off[i] = make_ulonglong2(o.full[i], o.tails[i]);
+    constexpr uint32_t per = kSortBuckets / kSmallMessages;
+    for (uint32_t k = m; k < kSortBuckets; k += kSmallMessages) cursor[k] = 0;
+    __syncthreads();
+    const uint64_t start = full * C, len = msg.nbytes - start;
+    const bool tail = m < n && (C == 0 || len != 0);
+    const uint32_t cls = block_class(sha_blocks(len));
+    if (tail) atomicAdd(&cursor[cls], 1u);
+    __syncthreads();
+    // thread t owns classes top down to top - per + 1: slots, largest class first
+    const uint32_t top = kSortBuckets - 1 - m * per, lane = m & 63;
+    uint32_t mine = 0;
+    for (uint32_t k = 0; k < per; ++k) mine += cursor[top - k];
+    uint32_t sum = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t below = __shfl_up(sum, d);
+        if (lane >= (uint32_t)d) sum += below;
+    }
+    if (lane == 63) wave_tails[m >> 6] = sum;
+    __syncthreads();
+    uint32_t pos = sum - mine;
+    for (uint32_t w = 0; w < m >> 6; ++w) pos += wave_tails[w];
+    for (uint32_t k = 0; k < per; ++k) {
+        const uint32_t c = cursor[top - k];
+        cursor[top - k] = pos;
+        pos += c;
+    }
+    __syncthreads();
+    if (tail) {
+        LeafDesc d;
+        d.src = msg.data + start;
+        d.nbytes = len;
+        d.out = (uint64_t)o.full[m] + o.tails[m] + full;
+        desc[n_full + atomicAdd(&cursor[cls], 1u)] = d;
+    }
+}
+
+// select_kernel over so few messages, without their counts and offsets.
+__global__ void __launch_bounds__(kSmallMessages) select_small_kernel(const MsgDesc* __restrict__ msgs, uint32_t n,
+                                                                      uint64_t C, const uint64_t* __restrict__ leaves,
+                                                                      uint64_t k, LeafDesc* __restrict__ desc) {
+    __shared__ SmallOffsets o;
+    uint64_t full;
+    small_offsets(msgs, n, C, o, &full);
+    for (uint64_t e = (uint64_t)blockIdx.x * kSmallMessages + threadIdx.x; e < k;
+         e += (uint64_t)gridDim.x * kSmallMessages) {
+        const uint64_t leaf = leaves[e];
+        uint32_t lo = 0, hi = n;  // as find_leaf_owner
+        while (hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if ((uint64_t)o.full[mid] + o.tails[mid] <= leaf) lo = mid; else hi = mid;
+        }
+        const uint64_t i = leaf - ((uint64_t)o.full[lo] + o.tails[lo]), nbytes = msgs[lo].nbytes;
+        LeafDesc d;
+        d.src = o.data[lo] + i * C;  // C == 0: i == 0
+        d.nbytes = C == 0 || nbytes - i * C < C ? nbytes - i * C : C;
+        d.out = leaf;
+        desc[e] = d;
+    }
+}
+
 unsigned grid_for(uint64_t n) {
     const uint64_t blocks = (n + kThreads - 1) / kThreads;
     const uint64_t cap = 65536;  // grid-stride loops cover the rest
@@ -364,6 +502,25 @@ hipError_t launch_sched_select(const MsgDesc* msgs, const Pair* off, uint32_t n,
                                uint64_t k, LeafDesc* desc, hipStream_t s) {
     if (k == 0) return hipSuccess;
     select_kernel<<<grid_for(k), kThreads, 0, s>>>(msgs, off, n, C, leaves, k, desc);
+    return hipGetLastError();
+}
+
+hipError_t launch_sched_small(const MsgDesc* msgs, uint32_t n, uint64_t C, uint64_t n_full, Pair* off, LeafDesc* desc,
+                              hipStream_t s) {
+    if (n == 0 || n > kSmallMessages) return hipErrorInvalidValue;
+    const uint64_t blocks = (n_full + kSmallMessages - 1) / kSmallMessages;
+    schedule_small_kernel<<<1 + (unsigned)(blocks < 1024 ? blocks : 1024), kSmallMessages, 0, s>>>(msgs, n, C, n_full,
+                                                                                                 off, desc);
+    return hipGetLastError();
+}
+
+hipError_t launch_select_small(const MsgDesc* msgs, uint32_t n, uint64_t C, const uint64_t* leaves, uint64_t k,
+                               LeafDesc* desc, hipStream_t s) {
+    if (n == 0 || n > kSmallMessages) return hipErrorInvalidValue;
+    if (k == 0) return hipSuccess;
+    const uint64_t blocks = (k + kSmallMessages - 1) / kSmallMessages;
+    select_small_kernel<<<(unsigned)(blocks < 1024 ? blocks : 1024), kSmallMessages, 0, s>>>(msgs, n, C, leaves, k,
+                                                                                           desc);
     return hipGetLastError();
 }
 
