@@ -496,7 +496,7 @@ hv_status schedule(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_bytes, bo
 
     const HashLayout& L = *L_out;
     if (!up->pending) {
-        const hipError_t e = hipMemcpyWithStream(L.msgs, msgs, sizeof(hv_msg) * n_msgs, hipMemcpyHostToDevice, stream);
+        const hipError_t e = upload_messages(L.msgs, msgs, n_msgs, stream);
         if (e != hipSuccess) return hip_fail(e, "descriptor upload");
     }
     st = hvh::queue_schedule(L.msgs, n_msgs, chunk_bytes, n_full, n_leaves, L, stream);
@@ -617,8 +617,7 @@ hv_status hv_merkle_reduce_alg(hv_alg alg, const uint8_t* nodes, const uint64_t*
     if ((st = merkle_plan(seg_offsets, n_seg, &table, &launches)) != HV_OK) return st;
 
     const MerkleLayout L = merkle_layout(workspace, n_nodes, n_seg, D);
-    const hipError_t e = hipMemcpyWithStream(L.table, table.data(), table.size() * sizeof(uint64_t),
-                                             hipMemcpyHostToDevice, stream);
+    const hipError_t e = hv::upload_table(L.table, table.data(), table.size(), stream);
     if (e != hipSuccess) return hip_fail(e, "plan upload");
     uint64_t outputs[kMaxMerkleLaunches];
     for (int k = 1; k <= launches; ++k) outputs[k - 1] = table[(size_t)k * row + n_seg];

@@ -63,6 +63,13 @@ inline bool tape_worth(uint32_t n_msgs, uint64_t n_leaves) {
     return n_leaves > 65536 && n_leaves <= (1u << 20) && n_msgs <= n_leaves / 4;
 }
 
+// A message table to the device; `msgs` is read before the call returns.
+inline hipError_t upload_messages(hv::MsgDesc* to, const hv_msg* msgs, uint32_t n_msgs, hipStream_t stream) {
+    static_assert(sizeof(hv_msg) == 2 * sizeof(uint64_t) && sizeof(hv::MsgDesc) == sizeof(hv_msg), "message layout");
+    return hv::upload_table(reinterpret_cast<uint64_t*>(to), reinterpret_cast<const uint64_t*>(msgs),
+                            2 * (size_t)n_msgs, stream);
+}
+
 // The leaf kernel of a scheduled table (L.desc, L.off): the automatic choice,
 // over a tape where `tape` (L's tape scratch is there) and it pays.
 hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,

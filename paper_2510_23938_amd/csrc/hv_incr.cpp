@@ -198,14 +198,11 @@ hv_status hv_tree_update_alg(hv_alg alg, const uint8_t* leaf_digests, const uint
     const TreeLayout T = tree_layout(tree, rows, n_seg, levels, D);
     const size_t w = (size_t)n_seg + 1;
     // the offset table is re-sent so the kernels walk exactly the layout planned here
-    hipError_t e =
-        hipMemcpyWithStream(T.table, rows.data(), rows.size() * sizeof(uint64_t), hipMemcpyHostToDevice, stream);
+    hipError_t e = hv::upload_table(T.table, rows.data(), rows.size(), stream);
     if (e != hipSuccess) return hip_fail(e, "table upload");
     if (n_dirty > 0) {
         const UpdateLayout U = update_layout(workspace, n_dirty);
-        if ((e = hipMemcpyWithStream(U.dirty, dirty, n_dirty * sizeof(uint64_t), hipMemcpyHostToDevice, stream)) !=
-            hipSuccess)
-            return hip_fail(e, "dirty list upload");
+        if ((e = hv::upload_table(U.dirty, dirty, n_dirty, stream)) != hipSuccess) return hip_fail(e, "dirty list upload");
         if ((e = hv::launch_tree_locate(U.dirty, n_dirty, T.table, n_seg, U.seg_of, U.local, stream)) != hipSuccess)
             return hip_fail(e, "locate");
         if ((e = hv::launch_tree_update_leaves(ka, leaf_digests, U.dirty, n_dirty, T.level[0], stream)) != hipSuccess)
@@ -252,9 +249,8 @@ hv_status hv_rehash_chunks_alg(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, 
     if (n_listed == 0) return HV_OK;
     const RehashLayout R = rehash_layout(workspace, n_msgs, n_listed);
     const HashLayout& L = R.hash;
-    hipError_t e = hipMemcpyWithStream(L.msgs, msgs, sizeof(hv_msg) * n_msgs, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyWithStream(R.list, leaves, n_listed * sizeof(uint64_t), hipMemcpyHostToDevice, stream);
+    hipError_t e = upload_messages(L.msgs, msgs, n_msgs, stream);
+    if (e == hipSuccess) e = hv::upload_table(R.list, leaves, n_listed, stream);
     if (e != hipSuccess) return hip_fail(e, "upload");
     if (n_msgs <= hv::kSmallMessages && n_leaves <= kMaxLeaves) {
         e = hv::launch_select_small(L.msgs, n_msgs, chunk_bytes, R.list, n_listed, L.desc, stream);

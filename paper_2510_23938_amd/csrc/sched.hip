@@ -460,6 +460,33 @@ __global__ void __launch_bounds__(kSmallMessages) select_small_kernel(const MsgD
     }
 }
 
+// Small host tables in a launch's arguments.
+constexpr uint32_t kArgBytes = 3840;  // of the 4 KB of arguments a launch is sure to take
+template <class W>
+struct ArgTable {
+    W w[kArgBytes / sizeof(W)];
+};
+
+template <class W>
+__global__ void __launch_bounds__(kThreads) arg_table_kernel(uint64_t* __restrict__ to, uint32_t n,
+                                                             const ArgTable<W> table) {
+    for (uint32_t i = threadIdx.x; i < n; i += kThreads) to[i] = table.w[i];
+}
+
+template <class W>
+hipError_t send_in_args(uint64_t* to, const uint64_t* from, size_t n, hipStream_t s) {
+    constexpr size_t kPer = kArgBytes / sizeof(W);
+    for (size_t at = 0; at < n; at += kPer) {
+        ArgTable<W> table;
+        const size_t k = n - at < kPer ? n - at : kPer;
+        for (size_t i = 0; i < k; ++i) table.w[i] = (W)from[at + i];
+        arg_table_kernel<W><<<1, kThreads, 0, s>>>(to + at, (uint32_t)k, table);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 unsigned grid_for(uint64_t n) {
     const uint64_t blocks = (n + kThreads - 1) / kThreads;
     const uint64_t cap = 65536;  // grid-stride loops cover the rest
@@ -471,6 +498,21 @@ unsigned grid_for(uint64_t n) {
 hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t s) {
     fill_u64_kernel<<<grid_for(n), kThreads, 0, s>>>(p, n, v);
     return hipGetLastError();
+}
+
+hipError_t upload_table(uint64_t* to, const uint64_t* from, size_t n, hipStream_t s) {
+    constexpr size_t kLaunches = 6;
+    if (n <= kLaunches * kArgBytes / sizeof(uint32_t)) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        const hipError_t e = hipStreamIsCapturing(s, &capture);
+        if (e != hipSuccess) return e;
+        uint64_t any = 0;
+        for (size_t i = 0; i < n; ++i) any |= from[i];
+        if (capture == hipStreamCaptureStatusNone && any >> 32 == 0) return send_in_args<uint32_t>(to, from, n, s);
+        if (capture == hipStreamCaptureStatusNone && n <= kLaunches * kArgBytes / sizeof(uint64_t))
+            return send_in_args<uint64_t>(to, from, n, s);
+    }
+    return hipMemcpyWithStream(to, from, n * sizeof(uint64_t), hipMemcpyHostToDevice, s);
 }
 
 hipError_t launch_sched_count(const MsgDesc* msgs, uint32_t n, uint64_t C, Pair* cnt, hipStream_t s) {

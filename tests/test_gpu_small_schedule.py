@@ -52,3 +52,22 @@ def test_rehash(n, C):
     others = torch.ones(k, dtype=torch.bool, device="cuda")
     others[at] = False
     assert not got[others].any()
+
+
+# Tables that fill a launch's arguments (480 words, 960 where they fit 32 bits)
+# or all six launches', and one message or leaf more.
+@pytest.mark.parametrize("n,k", [(240, 960), (241, 961), (1440, 5760), (1441, 5761)])
+def test_tables_in_arguments(n, k):
+    lens = np.full(n, 128 * 6, dtype=np.uint64)
+    buf = torch.zeros(int(lens.sum()), dtype=torch.uint8, device="cuda").random_(0, 256)
+    ptrs = np.uint64(buf.data_ptr()) + np.arange(n, dtype=np.uint64) * np.uint64(128 * 6)
+    want, seg = hv.hv_hash_chunks((ptrs, lens), 128)
+    leaves = np.sort(np.random.default_rng(n).choice(6 * n, k, replace=False)).astype(np.uint64)
+    at = torch.from_numpy(leaves.astype(np.int64)).cuda()
+    got = want.clone()
+    got[at] = 0
+    tree = hv.Tree(got, seg)
+    hv.hv_rehash_chunks((ptrs, lens), 128, leaves, got)
+    roots = tree.update(got, leaves)
+    assert torch.equal(got, want)
+    assert torch.equal(roots, hv.hv_merkle_reduce(want, seg))
