@@ -27,9 +27,9 @@
 //    -- against 14 for a round on one lane; the two steps of lag and the
 //    selects at a block's ends add 26 to its 576.
 //
-// One 64 KiB chunk takes 1.31 ms (1.28 us per block, 4.8 cycles per
+// One 64 KiB chunk takes 1.18 ms (1.15 us per block, 4.6 cycles per
 // instruction) against 1.79 with one lane per chunk and 2.65 with the one-wave
-// kernel, whatever the number of chunks up to 64 per CU; up to 128 per CU 1.70
+// kernel, whatever the number of chunks up to 64 per CU; up to 128 per CU 1.60
 // against 1.88 and 2.69.
 //
 // A workgroup holds kGroups groups of 64 chunks, four waves each: two
@@ -139,7 +139,7 @@ __device__ __forceinline__ void whole_block_words(const uint32_t D[17], uint32_t
 // waits.  Every producer passes barriers 0..nmax.
 template <bool kAligned>
 __device__ __forceinline__ void produce_all(uint32_t p, uint64_t src, uint64_t total, uint32_t nfull, uint32_t r,
-                                            uint32_t nblk, uint32_t nmax, uint32_t nfull_min, uint32_t lane,
+                                            uint32_t nblk, uint32_t nmax, uint32_t lane,
                                             uint4 (*sched)[16][kRow]) {
     const uint32_t sh = kAligned ? 0u : (uint32_t)(src & 3);
     uint32_t D[2][17];
@@ -162,10 +162,10 @@ __device__ __forceinline__ void produce_all(uint32_t p, uint64_t src, uint64_t t
                 wait_vmem();  // `cur` has landed; the loads below stay in flight
                 if (b + 2 < nblk) load_block<kAligned>(src, block_valid(nfull, r, b + 2), b + 2, nxt);
                 uint32_t W[16];
-                if (b < nfull_min)
-                    whole_block_words(cur, sh, W);
-                else
+                if (__any(b - nfull < (r <= 55 ? 1u : 2u)))  // padding in this block of some chunk
                     block_words(cur, sh, total, nfull, r, b, W);
+                else
+                    whole_block_words(cur, sh, W);
                 uint4(*buf)[kRow] = sched[slot];
                 slot = slot == 0 ? 2 : slot - 1;  // (b + 2) % 3
 #pragma unroll
@@ -198,17 +198,69 @@ struct Half {
 
 // Step s of the lanes' shared recurrence (see the top of the file): R[(i - s) & 3]
 // is the lane's value i steps old, and the new value takes the oldest one's place.
-__device__ __forceinline__ void step(uint32_t R[4], int s, const Half& c, uint32_t kw) {
-    const uint32_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3], x3 = R[(3 - s) & 3];
-    const uint32_t sigma = xor3(rotr(x0, c.r1), rotr(x0, c.r2), rotr(x0, c.r3));
-    const uint32_t p = __builtin_amdgcn_bitop3_b32(x0, x1, c.m, 0x2D);  // a ^ b, or ~e
-    const uint32_t f = choose(p, x2, x1);                               // Maj(a, b, c), or Ch(e, f, g)
-    uint32_t q;                                                         // -d, or h + K + W: (x3 ^ m) + kw
-    // the compiler would split this into an XOR and share the addition with
-    // the next one, and the lane exchange then needs an instruction of its own
+// q: this step's -d or h + K + W and the partner's value, formed in the step
+// before; its place is taken by the next step's (words next_kw).
+//
+// The order is fixed here: an instruction that needs the one before it issues
+// 8 cycles after it, one that needs the second before 6 after that, and at a
+// distance of four nothing is lost, so the nine are interleaved such that none
+// needs the one before it.  The compiler's order had three that did, and waits
+// before DPP operands: 1.31 us per block, 1.15 with this one and place_code.
+#define HV_PIN __builtin_amdgcn_sched_barrier(0)
+__device__ __forceinline__ uint32_t own_part(uint32_t x3, const Half& c, uint32_t kw) {
+    uint32_t q;  // (x3 ^ m) + kw; the compiler would split this and share the addition with another
     asm("v_xad_u32 %0, %1, %2, %3" : "=v"(q) : "v"(x3), "v"(c.m), "v"(kw));
-    q += __builtin_amdgcn_update_dpp(0, x1, 0xB1, 0xf, 0xf, true);  // the partner's x1: quad_perm [1,0,3,2]
+    return q;
+}
+// q plus the chunk's other lane's x1; written out for the same reason.  A DPP
+// operand may be read no sooner than two instructions after it is written:
+// `fresh` waits that out, elsewhere x1 is a step old.
+template <bool fresh>
+__device__ __forceinline__ uint32_t add_partner(uint32_t q, uint32_t x1) {
+    uint32_t r;
+    if constexpr (fresh)
+        asm("s_nop 1\n\tv_add_u32_dpp %0, %1, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+            : "=v"(r) : "v"(x1), "v"(q));
+    else
+        asm("v_add_u32_dpp %0, %1, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x1), "v"(q));
+    return r;
+}
+__device__ __forceinline__ void step(uint32_t R[4], int s, const Half& c, uint32_t& q, uint32_t next_kw) {
+    const uint32_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3];
+    const uint32_t i = rotr(x0, c.r1);
+    HV_PIN;
+    const uint32_t j = rotr(x0, c.r2);
+    HV_PIN;
+    const uint32_t k = rotr(x0, c.r3);
+    HV_PIN;
+    const uint32_t p = __builtin_amdgcn_bitop3_b32(x0, x1, c.m, 0x2D);  // a ^ b, or ~e
+    HV_PIN;
+    const uint32_t sigma = xor3(i, j, k);
+    HV_PIN;
+    const uint32_t f = choose(p, x2, x1);  // Maj(a, b, c), or Ch(e, f, g)
+    HV_PIN;
+    const uint32_t next = own_part(x2, c, next_kw);
+    HV_PIN;
     R[(3 - s) & 3] = sigma + f + q;
+    HV_PIN;
+    q = add_partner<false>(next, x0);
+    HV_PIN;
+}
+
+// The place of the code that follows, all of it 8-byte instructions: on an
+// 8-byte boundary a wave alone on its SIMD issues one every 4.6 cycles, and off
+// it every 5.5 (1.18 ms for 64 KiB chunks, and 1.42).  Where a producer shares
+// the SIMD it is off the boundary on purpose: the consumer, the older wave, is
+// issued first, and at the full rate leaves its producer too few slots (1.89
+// ms, and 1.59; with priority for the producer 1.78).
+template <bool kAlone>
+__device__ __forceinline__ void place_code() {
+    HV_PIN;
+    if constexpr (kAlone)
+        asm volatile(".p2align 3");
+    else
+        asm volatile(".p2align 3\n\ts_nop 0");
+    HV_PIN;
 }
 
 // The 64 rounds of one block on its words q (FIPS 180-4 section 6.2.2 steps
@@ -216,20 +268,28 @@ __device__ __forceinline__ void step(uint32_t R[4], int s, const Half& c, uint32
 // (H4, H5, H6, H7) in e lanes and (H2, H3, H0, H1) in a lanes, so that the
 // values of step 64 feed forward into H[0] and H[1] in both; the feed-forward
 // only where `on` (the lane still has blocks).
+template <bool kAlone>
 __device__ __forceinline__ void rounds(uint32_t H[4], const uint4 q[16], const Half& c, bool on) {
     uint32_t R[4] = {H[0], H[1], H[2], H[3]}, at64[4];
+    uint32_t own = add_partner<true>(own_part(R[3], c, q[0].x), R[1]);
+    place_code<kAlone>();
 #pragma unroll
     for (int s = 0; s < 66; ++s) {
-        const uint4 w = q[(s >> 2) & 15];
-        const uint32_t kw = s >= 64 ? 1u : (s & 3) == 0 ? w.x : (s & 3) == 1 ? w.y : (s & 3) == 2 ? w.z : w.w;
+        const uint4 w = q[((s + 1) >> 2) & 15];
+        const int k = (s + 1) & 3;
+        const uint32_t next_kw = s + 1 >= 64 ? 1u : k == 0 ? w.x : k == 1 ? w.y : k == 2 ? w.z : w.w;
         if (s == 64)
 #pragma unroll
             for (int i = 0; i < 4; ++i) at64[i] = R[i];
-        step(R, s, c, kw);
+        step(R, s, c, own, next_kw);
         // the a lanes' first two values are the block's b and a themselves
         if (s == 0) R[3] = c.m ? H[3] : R[3];
-        if (s == 1) R[2] = c.m ? H[2] : R[2];
+        if (s == 1) {
+            R[2] = c.m ? H[2] : R[2];
+            place_code<kAlone>();
+        }
     }
+#undef HV_PIN
     if (on) {
         H[0] += at64[0];
         H[1] += at64[1];
@@ -241,6 +301,7 @@ __device__ __forceinline__ void rounds(uint32_t H[4], const uint4 q[16], const H
 // A consumer's work for block b (its words in `cur`): pass the barrier of
 // block b + 1 and issue the reads of its words into `nxt`, then run block b's
 // rounds, so the reads land under the rounds.  buf: b % 3, moved on.
+template <bool kAlone>
 __device__ __forceinline__ void consume(uint32_t b, uint32_t& buf, uint32_t nmax, uint32_t nblk, uint32_t col,
                                         uint4 (*sched)[16][kRow], uint32_t H[4], const Half& c, const uint4 cur[16],
                                         uint4 nxt[16]) {
@@ -254,7 +315,7 @@ __device__ __forceinline__ void consume(uint32_t b, uint32_t& buf, uint32_t nmax
 #pragma unroll
         for (int g = 0; g < 16; ++g) nxt[g] = sched[buf][g][col];
     }
-    rounds(H, cur, c, b < nblk);
+    rounds<kAlone>(H, cur, c, b < nblk);
 }
 
 template <int kGroups>
@@ -275,7 +336,7 @@ __global__ void __launch_bounds__(256 * kGroups) sha256_chain_kernel(const LeafD
     uint32_t nblk = live ? nfull + (r <= 55 ? 1u : 2u) : 0u;
     // every wave of the workgroup runs the same number of barriers: the most
     // blocks of any of its chunks
-    uint32_t nmax = nblk, nfull_min = live ? nfull : 0xffffffffu;
+    uint32_t nmax = nblk;
     if constexpr (kGroups == 2) {
         const uint64_t other = ((uint64_t)blockIdx.x * kGroups + (group ^ 1)) * 64 + lane;
         if (other < n_slots) {
@@ -286,21 +347,19 @@ __global__ void __launch_bounds__(256 * kGroups) sha256_chain_kernel(const LeafD
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(nfull_min, o);
+        const uint32_t x = __shfl_xor(nmax, o);
         nmax = x > nmax ? x : nmax;
-        nfull_min = y < nfull_min ? y : nfull_min;
     }
     nmax = __builtin_amdgcn_readfirstlane(nmax);
-    nfull_min = __builtin_amdgcn_readfirstlane(nfull_min);
 
     if (wave >= 2 * kGroups) {
         // the ones of this producer's group (each writes half, before barrier 1)
         const uint32_t p = wave & 1;
         if (lane < 24) sched[group][(24 * p + lane) >> 4][(24 * p + lane) & 15][64] = make_uint4(1, 1, 1, 1);
         if (__all((d.src & 15) == 0))
-            produce_all<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[group]);
+            produce_all<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, lane, sched[group]);
         else
-            produce_all<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched[group]);
+            produce_all<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, lane, sched[group]);
         return;
     }
     const uint32_t chunk = 32 * (wave & 1) + (lane >> 1);
@@ -326,8 +385,8 @@ __global__ void __launch_bounds__(256 * kGroups) sha256_chain_kernel(const LeafD
     }
     uint32_t buf = 0;  // b % 3
     for (uint32_t b = 0; b < nmax; b += 2) {
-        consume(b, buf, nmax, nblk, col, sched[group], H, c, A, B);
-        if (b + 1 < nmax) consume(b + 1, buf, nmax, nblk, col, sched[group], H, c, B, A);
+        consume<kGroups == 1>(b, buf, nmax, nblk, col, sched[group], H, c, A, B);
+        if (b + 1 < nmax) consume<kGroups == 1>(b + 1, buf, nmax, nblk, col, sched[group], H, c, B, A);
     }
     if (live && d.out < out_bound) {
         uint4* out = reinterpret_cast<uint4*>(digests + 32 * d.out);
@@ -556,7 +615,7 @@ int leaf_kernel_for(uint64_t n_slots, bool background) {
     const int choice = leaf_kernel_choice();
     const uint64_t cus = device_cus();
     // the two-wave kernels while every CU holds one workgroup at most: 64
-    // KiB chunks take 1.31 ms up to 64 per CU and 1.70 up to 128, against 2.69
+    // KiB chunks take 1.18 ms up to 64 per CU and 1.60 up to 128, against 2.69
     // with the one-wave kernel; with more, two workgroups share a CU and the
     // one-wave kernel (or SHA-256's three-group one, launch_sha256_auto) is
     // faster.  Background work keeps the one-wave kernel:

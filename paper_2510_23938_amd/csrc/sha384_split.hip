@@ -19,9 +19,9 @@
 // partner's value 2 (an addition with DPP operands) and 2 additions.  A
 // workgroup is 64 chunks, two consumers and two producers, a SIMD each; three
 // buffers of 40 x 65 16-byte entries are 122 KB of its CU's LDS.
-// 9,500 chunks of 256 KiB, with the reductions above them: 6.66 ms (3.2 us and
-// 1565 instructions per block) against 9.39 with one lane per chunk and one
-// producer (2163 instructions).
+// 9,225 chunks of 256 KiB, with the reductions above them: 6.24 ms (3.0 us and
+// 1570 instructions per block) against 9.39 with one lane per chunk and one
+// producer (2163 instructions).  The compiler's order of a step took 6.66.
 //
 // Up to 128 chunks per CU: the two-pair kernel, one lane per chunk.  A
 // producer wave loads each block one block ahead, builds its 16 message words
@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(256) sha384_pairs_kernel(const LeafDesc* __res
 // passes barriers 0..nmax.
 template <bool kAligned>
 __device__ __forceinline__ void produce_alternate(uint32_t p, uint64_t src, uint64_t total, uint32_t nfull, uint32_t r,
-                                                  uint32_t nblk, uint32_t nmax, uint32_t nfull_min, uint32_t lane,
+                                                  uint32_t nblk, uint32_t nmax, uint32_t lane,
                                                   uint4 (*sched)[kEntries][kRow]) {
     const uint32_t sh = kAligned ? 0u : (uint32_t)(src & 3);
     uint32_t D[2][33];
@@ -269,10 +269,10 @@ __device__ __forceinline__ void produce_alternate(uint32_t p, uint64_t src, uint
                 wait_vmem();  // `cur` has landed; the loads below stay in flight
                 if (b + 2 < nblk) load_block<kAligned>(src, block_valid(nfull, r, b + 2), b + 2, nxt);
                 uint64_t W[16];
-                if (b < nfull_min)
-                    whole_block_words(cur, sh, W);
-                else
+                if (__any(b - nfull < (r <= 111 ? 1u : 2u)))  // padding in this block of some chunk
                     block_words(cur, sh, total, nfull, r, b, W);
+                else
+                    whole_block_words(cur, sh, W);
                 uint4(*buf)[kRow] = sched[slot];
                 slot = slot == 0 ? 2 : slot - 1;  // (b + 2) % 3
 #pragma unroll
@@ -308,52 +308,88 @@ __device__ __forceinline__ uint64_t rotr64_below_32(uint64_t x, uint32_t n) {
     return pack(__builtin_amdgcn_alignbit(lo32(x), hi32(x), n), __builtin_amdgcn_alignbit(hi32(x), lo32(x), n));
 }
 
+#define HV_PIN __builtin_amdgcn_sched_barrier(0)
+
+// (x3 ^ m) + kw: a step's -d, or h + K + W.
+__device__ __forceinline__ uint64_t own_part(uint64_t x3, const Half& c, uint64_t kw) {
+    // the XOR as an 8-byte instruction (see place_code)
+    const uint64_t x = pack(__builtin_amdgcn_bitop3_b32(hi32(x3), c.m, c.m, 0x3C),
+                            __builtin_amdgcn_bitop3_b32(lo32(x3), c.m, c.m, 0x3C));
+    HV_PIN;
+    return x + kw;
+}
+
 // x plus the chunk's other lane's y.  A DPP operand may be read no sooner than
 // two instructions after it is written, and the compiler does not see into the
-// block: `after`, a value computed from y by several instructions, keeps it
-// that far behind, and where there is none (`fresh`) the block waits itself.
+// block: `fresh` waits that out, elsewhere y is a step old.
 template <bool fresh>
-__device__ __forceinline__ uint64_t add_partner(uint64_t x, uint64_t y, uint64_t after) {
+__device__ __forceinline__ uint64_t add_partner(uint64_t x, uint64_t y) {
     uint32_t lo, hi;
-    if constexpr (fresh)
-        asm("s_nop 1\n\t"
-            "v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-            "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-            : "=&v"(lo), "=v"(hi) : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)) : "vcc");
-    else
-        asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-            "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-            : "=&v"(lo), "=v"(hi)
-            : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)), "v"(lo32(after))
-            : "vcc");
+    if constexpr (fresh) asm volatile("s_nop 1");
+    HV_PIN;
+    asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=&v"(lo), "=v"(hi) : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)) : "vcc");
     return pack(hi, lo);
 }
 
 // Step s of the lanes' shared recurrence: R[(i - s) & 3] is the lane's value i
-// steps old, and the new value takes the oldest one's place.  Four instructions
-// depend on each other from one step to the next (a dependent one issues 8
-// cycles later): the partner's value joins h + K + W, off that path.
+// steps old, and the new value takes the oldest one's place.  q: this step's
+// -d or h + K + W and the partner's value, formed in the step before; its place
+// is taken by the next step's (word next_kw).  The order is fixed, as in
+// sha256_split.hip, with two or more instructions between any and the one that
+// needs it.
 template <int s>
-__device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t kw) {
-    const uint64_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3], x3 = R[(3 - s) & 3];
-    const uint64_t m = pack(c.m, c.m);
-    const uint64_t sigma = rotr64_below_32(bitop3_64<0x96>(x0, rotr64_below_32(x0, c.r1), rotr64_below_32(x0, c.r2)),
-                                           c.r3);
-    const uint64_t p = bitop3_64<0x2D>(x0, x1, m);   // a ^ b, or ~e
-    const uint64_t f = bitop3_64<0xCA>(p, x2, x1);   // Maj(a, b, c), or Ch(e, f, g)
-    const uint64_t q = pack(hi32(x3) ^ c.m, lo32(x3) ^ c.m) + kw;  // -d, or h + K + W
-    R[(3 - s) & 3] = sigma + (f + add_partner<s == 0>(q, x1, x0));
+__device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t& q, uint64_t next_kw) {
+    const uint64_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3];
+    const uint64_t n = pack(__builtin_amdgcn_bitop3_b32(hi32(x2), c.m, c.m, 0x3C),
+                            __builtin_amdgcn_bitop3_b32(lo32(x2), c.m, c.m, 0x3C));  // as own_part
+    HV_PIN;
+    const uint64_t i = rotr64_below_32(x0, c.r1);
+    HV_PIN;
+    const uint64_t j = rotr64_below_32(x0, c.r2);
+    HV_PIN;
+    const uint64_t p = bitop3_64<0x2D>(x0, x1, pack(c.m, c.m));  // a ^ b, or ~e
+    HV_PIN;
+    const uint64_t own = n + next_kw;
+    HV_PIN;
+    const uint64_t y = bitop3_64<0x96>(x0, i, j);
+    HV_PIN;
+    const uint64_t f = bitop3_64<0xCA>(p, x2, x1);  // Maj(a, b, c), or Ch(e, f, g)
+    HV_PIN;
+    const uint64_t sigma = rotr64_below_32(y, c.r3);
+    HV_PIN;
+    const uint64_t t = f + q;
+    HV_PIN;
+    q = add_partner<false>(own, x0);
+    HV_PIN;
+    R[(3 - s) & 3] = sigma + t;
+    HV_PIN;
 }
 
+// The place of the code that follows, all of it 8-byte instructions: on an
+// 8-byte boundary a wave alone on its SIMD issues faster (sha256_split.hip).
+__device__ __forceinline__ void place_code() {
+    HV_PIN;
+    asm volatile(".p2align 3");
+    HV_PIN;
+}
+
+// Steps s to end - 1, word s + 1 of the schedule (a pair per entry) from `q`, or
+// from `after` for the first of the next sixteen (ones after the last).
 template <int s, int end>
-__device__ __forceinline__ void steps(uint64_t R[4], const uint64_t H[4], const Half& c, const uint4 q[8]) {
+__device__ __forceinline__ void steps(uint64_t R[4], const uint64_t H[4], const Half& c, uint64_t& own,
+                                      const uint4 q[8], const uint4 after[8]) {
     if constexpr (s < end) {
-        const uint4 w = q[(s >> 1) & 7];
-        step<s>(R, c, s & 1 ? pack(w.w, w.z) : pack(w.y, w.x));
+        const uint4 w = s + 1 < end ? q[((s + 1) >> 1) & 7] : after[0];
+        step<s>(R, c, own, s + 1 >= 80 ? 1 : s & 1 ? pack(w.y, w.x) : pack(w.w, w.z));
         // the a lanes' first two values are the block's b and a themselves
         if (s == 0) R[3] = c.m ? H[3] : R[3];
-        if (s == 1) R[2] = c.m ? H[2] : R[2];
-        steps<s + 1, end>(R, H, c, q);
+        if (s == 1) {
+            R[2] = c.m ? H[2] : R[2];
+            place_code();
+        }
+        steps<s + 1, end>(R, H, c, own, q, after);
     }
 }
 
@@ -370,32 +406,38 @@ __device__ __forceinline__ void consume(uint32_t b, uint32_t& slot, uint32_t nma
     auto read = [&](uint32_t from, int j, uint4 q[8]) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] = sched[from][8 * j + e][col];
-        __builtin_amdgcn_sched_barrier(0);
     };
     wait_lds();
+    uint64_t own = add_partner<true>(own_part(R[3], c, pack(cur[0].y, cur[0].x)), R[1]);
     read(slot, 1, nxt);
-    steps<0, 16>(R, H, c, cur);
+    place_code();
+    steps<0, 16>(R, H, c, own, cur, nxt);
     wait_lds();
     read(slot, 2, cur);
-    steps<16, 32>(R, H, c, nxt);
+    place_code();
+    steps<16, 32>(R, H, c, own, nxt, cur);
     wait_lds();
     read(slot, 3, nxt);
-    steps<32, 48>(R, H, c, cur);
+    place_code();
+    steps<32, 48>(R, H, c, own, cur, nxt);
     wait_lds();
     read(slot, 4, cur);
-    steps<48, 64>(R, H, c, nxt);
+    place_code();
+    steps<48, 64>(R, H, c, own, nxt, cur);
     wait_lds();
     slot = slot == 2 ? 0 : slot + 1;
     if (b + 1 < nmax) {
         lds_barrier();  // barrier b + 2: block b + 1's words are in its buffer
         read(slot, 0, nxt);
     }
-    steps<64, 80>(R, H, c, cur);
+    place_code();
+    steps<64, 80>(R, H, c, own, cur, nxt);
     uint64_t at80[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) at80[i] = R[i];
-    step<80>(R, c, 1);
-    step<81>(R, c, 1);
+    step<80>(R, c, own, 1);
+    step<81>(R, c, own, 1);
+#undef HV_PIN
     if (b < nblk) {
         H[0] += at80[0];
         H[1] += at80[1];
@@ -417,24 +459,22 @@ __global__ void __launch_bounds__(256) sha384_chain_kernel(const LeafDesc* __res
     if (live) d = desc[slot];
     uint32_t nfull = (uint32_t)(d.nbytes >> 7), r = (uint32_t)(d.nbytes & 127);
     uint32_t nblk = live ? nfull + (r <= 111 ? 1u : 2u) : 0u;
-    uint32_t nmax = nblk, nfull_min = live ? nfull : 0xffffffffu;
+    uint32_t nmax = nblk;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t x = __shfl_xor(nmax, o), y = __shfl_xor(nfull_min, o);
+        const uint32_t x = __shfl_xor(nmax, o);
         nmax = x > nmax ? x : nmax;
-        nfull_min = y < nfull_min ? y : nfull_min;
     }
     nmax = __builtin_amdgcn_readfirstlane(nmax);
-    nfull_min = __builtin_amdgcn_readfirstlane(nfull_min);
 
     if (wave >= 2) {
         const uint32_t p = wave & 1;
         // the ones, each producer's half of them before barrier 1
         if (lane < 60) sched[(60 * p + lane) / kEntries][(60 * p + lane) % kEntries][64] = make_uint4(1, 0, 1, 0);
         if (__all((d.src & 15) == 0))
-            produce_alternate<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched);
+            produce_alternate<true>(p, d.src, d.nbytes, nfull, r, nblk, nmax, lane, sched);
         else
-            produce_alternate<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, nfull_min, lane, sched);
+            produce_alternate<false>(p, d.src, d.nbytes, nfull, r, nblk, nmax, lane, sched);
         return;
     }
     const uint32_t chunk = 32 * wave + (lane >> 1);
