@@ -98,6 +98,13 @@ enum { HV_SHA256 = 0, HV_SHA384 = 1 };
 hv_status hv_leaf_layout(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_bytes,
                          uint64_t* seg_offsets, uint64_t* n_leaves);
 
+/* msgs[i] = {data[i], nbytes[i]} for i < n_msgs: the message array of addresses
+ * and lengths kept apart, filled by several host threads where it is large.
+ *   data:   host array of device addresses.   nbytes: host array of lengths.
+ *   msgs:   host array, written.
+ * Errors: HV_ERR_INVALID_ARG for a NULL array with n_msgs > 0. */
+hv_status hv_pack_messages(const uint64_t* data, const uint64_t* nbytes, uint32_t n_msgs, hv_msg* msgs);
+
 /* Workspace bytes hv_hash_chunks needs for n_msgs messages with n_leaves
  * leaves in total (from hv_leaf_layout); 0 (and hv_last_error set) for more
  * than 2^31 leaves.  For 65537 to 2^20 leaves of at most a quarter as many

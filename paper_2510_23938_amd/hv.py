@@ -45,7 +45,7 @@ _STATUS = {1: "HV_ERR_INVALID_ARG", 2: "HV_ERR_WORKSPACE", 3: "HV_ERR_HIP"}
 
 # exported symbols, in the order include/hv.h declares them
 EXPORTS = (
-    "hv_leaf_layout", "hv_hash_workspace_bytes", "hv_hash_chunks", "hv_merkle_workspace_bytes",
+    "hv_leaf_layout", "hv_pack_messages", "hv_hash_workspace_bytes", "hv_hash_chunks", "hv_merkle_workspace_bytes",
     "hv_merkle_reduce", "hv_verify_workspace_bytes", "hv_verify_root", "hv_compare_roots",
     "hv_hash_chunks_alg", "hv_merkle_workspace_bytes_alg", "hv_merkle_reduce_alg", "hv_verify_root_alg",
     "hv_compare_roots_alg", "hv_hash_chunks_noalloc", "hv_last_error", "hv_set_kernel_timing", "hv_leaf_kernel_ms",
@@ -107,6 +107,7 @@ def _load():
     vp, u32, u64, sz = ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_size_t
     sig = {
         "hv_leaf_layout": ([vp, u32, u64, vp, vp], ctypes.c_int),
+        "hv_pack_messages": ([vp, vp, u32, vp], ctypes.c_int),
         "hv_hash_workspace_bytes": ([u32, u64], sz),
         "hv_hash_chunks": ([vp, u32, u64, vp, vp, sz, vp], ctypes.c_int),
         "hv_merkle_workspace_bytes": ([u64, u32], sz),
@@ -253,6 +254,17 @@ def _msg_array(ptrs: np.ndarray, lens: np.ndarray, host: HostBuffer | None = Non
     return arr
 
 
+def _packed_msgs(ptrs, lens, host: HostBuffer | None = None) -> np.ndarray:
+    """As _msg_array, filled by the library where the arrays can be handed over as they are."""
+    if not all(isinstance(a, np.ndarray) and a.dtype == np.uint64 and a.ndim == 1 and a.flags.c_contiguous
+               and len(a) == len(lens) for a in (ptrs, lens)):
+        return _msg_array(ptrs, lens, host)
+    n = len(lens)
+    arr = host.get(16 * n).reshape(n, 2) if host is not None else np.empty((n, 2), dtype=np.uint64)
+    _check(lib.hv_pack_messages(ptrs.ctypes.data, lens.ctypes.data, n, arr.ctypes.data))
+    return arr
+
+
 def messages_of(tensors) -> tuple:
     """(ptrs, lens) of contiguous device tensors' bytes, in the given order."""
     ptrs, lens = [], []
@@ -347,7 +359,7 @@ def hv_hash_chunks(msgs, chunk_bytes: int, device="cuda", workspace: Workspace |
         arr, seg, n_leaves = table
     else:
         ptrs, lens = _ptr_len(msgs)
-        arr = _msg_array(ptrs, lens, host)
+        arr = _packed_msgs(ptrs, lens, host)
         seg, n_leaves = _layout_of(arr, chunk_bytes, seg_host)
     n = len(arr)
     dev = torch.device(device)
