@@ -364,7 +364,7 @@ hv_status merkle_launch_kinds(hv_alg alg, const uint64_t* seg_offsets, uint32_t 
         const bool grouped = merkle_grouped(entries, n_seg, k);
         kind[k - 1] = grouped ? 1 : 2;
         units[k - 1] = out;
-        one_lane[k - 1] = grouped ? merkle_group_main(out, k == 1, alg == HV_SHA384, cus) : 0;
+        one_lane[k - 1] = grouped ? merkle_group_main(out, entries, k == 1, alg == HV_SHA384, cus) : 0;
     }
     return HV_OK;
 }
@@ -383,7 +383,7 @@ hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64
         hipError_t e;
         if (merkle_grouped(entries, n_seg, k)) {
             if (cus == 0 && (e = stream_cus(stream, &cus)) != hipSuccess) return hip_fail(e, "device query");
-            const uint64_t n_main = merkle_group_main(outputs[k - 1], k == 1, alg == HV_SHA384, cus);
+            const uint64_t n_main = merkle_group_main(outputs[k - 1], entries, k == 1, alg == HV_SHA384, cus);
             e = hv::launch_merkle_groups(a, in, dst, in_off, out_off, n_seg, outputs[k - 1], n_main, k == 1, stream);
         } else {
             e = hv::launch_merkle_tiles(a, in, dst, in_off, out_off, n_seg, outputs[k - 1], k == 1, stream);

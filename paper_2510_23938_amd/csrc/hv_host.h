@@ -146,14 +146,16 @@ hv_status merkle_launch_kinds(hv_alg alg, const uint64_t* seg_offsets, uint32_t 
 // ceil(G / R) * D on the busiest SIMD; the split keeps floor(G / R) whole
 // rounds and spreads the rest as four-lane waves, k * D + ceil(4r / R) * d.
 // The split is taken when it costs less: it shortens the launch's last round,
-// where one wave per SIMD would otherwise run alone.
-inline uint64_t merkle_group_main(uint64_t n_groups, bool leaf_mode, bool sha384, uint32_t cus) {
+// where one wave per SIMD would otherwise run alone.  A launch of less than a
+// round is all four-lane for many short segments (there is nothing else on the
+// chip) and all one-lane from kGroupMinNodes entries on.
+inline uint64_t merkle_group_main(uint64_t n_groups, uint64_t entries, bool leaf_mode, bool sha384, uint32_t cus) {
     if (cus == 0) return n_groups;
     const uint64_t leaf = leaf_mode ? 1 : 0, node = sha384 ? 1 : 2;  // 64- or 128-byte blocks per hash
     const uint64_t D = 8 * leaf + 7 * node, d = 2 * leaf + 3 * node;
     const uint64_t R = 256 * (uint64_t)cus;
     const uint64_t k = n_groups / R, r = n_groups % R;
-    if (r == 0) return n_groups;
+    if (r == 0 || (k == 0 && entries >= kGroupMinNodes)) return n_groups;
     const uint64_t all = (k + 1) * D, split = k * D + (4 * r + R - 1) / R * d;
     return split < all ? k * R : n_groups;
 }
