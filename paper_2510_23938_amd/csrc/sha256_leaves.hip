@@ -27,13 +27,13 @@
 #include "balance.h"
 #include "hv_kernels.h"
 #include "sha256_device.h"
+#include "stage.h"
 
 namespace hv {
 namespace {
 
 constexpr int kThreads = 256;                     // four waves per workgroup
 constexpr int kWaves = kThreads / 64;
-constexpr int kStageBytes = 128;                  // bytes per chunk per stage
 constexpr int kRowsPerLoad = 1024 / kStageBytes;  // chunks covered by one 64-lane 16-byte load
 
 // Swizzle of a chunk's 16-byte slots within its LDS row.  Consecutive lanes
@@ -56,7 +56,7 @@ __device__ __forceinline__ void wait_lgkm_all() { __builtin_amdgcn_s_waitcnt(0xC
 // Whole blocks of the wave's 64 chunks (every lane's chunk 16-byte aligned),
 // staged through this wave's 8 KB LDS row buffer.  nfull: this lane's whole
 // blocks (at most 2^31 under the library's chunk-size limit, so the block
-// counts below cannot wrap).
+// counts below cannot wrap; byte offsets take 64 bits).
 __device__ __forceinline__ void full_blocks_lds(uint32_t H[8], uint64_t src, uint32_t nfull, uint8_t* rows) {
     uint32_t lane = threadIdx.x & 63;
     // opaque, so that in a kernel that calls this in a loop the addresses
@@ -103,7 +103,7 @@ __device__ __forceinline__ void full_blocks_lds(uint32_t H[8], uint64_t src, uin
         wait_lgkm_all();  // and in VGPRs: the buffer may be refilled
         const uint32_t nx = st + 1;
         if (nx < stages) {
-            const uint32_t off = kStageBytes * nx;
+            const uint64_t off = stage_offset(nx);
             if (uniform && 2 * nx + 1 < nmax) {  // whole stage valid for every chunk
 #pragma unroll
                 for (int j = 0; j < kRowsPerLoad; ++j)
@@ -212,7 +212,7 @@ __device__ __forceinline__ void full_blocks_any(uint32_t H[8], uint64_t src, uin
         first = make_uint4(D[32], D[33], D[34], D[35]);
         const uint32_t nx = st + 1;
         if (nx < stages) {
-            const uint64_t off = (uint64_t)kStageBytes * nx;
+            const uint64_t off = stage_offset(nx);
             if (nx < all) {
 #pragma unroll
                 for (int j = 0; j < kRowsPerLoad; ++j)

@@ -11,13 +11,13 @@
 #include "balance.h"
 #include "hv_kernels.h"
 #include "sha384_device.h"
+#include "stage.h"
 
 namespace hv {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kStageBytes = 128;
 constexpr int kRowsPerLoad = 1024 / kStageBytes;
 
 __device__ __forceinline__ uint32_t swizzle(uint32_t c) { return (c ^ (c >> 3)) & 7u; }
@@ -74,7 +74,7 @@ __device__ __forceinline__ void full_blocks_lds(uint64_t H[8], uint64_t src, uin
         wait_lgkm_all();
         const uint32_t nx = b + 1;
         if (nx < nmax) {
-            const uint64_t off = (uint64_t)kStageBytes * nx;
+            const uint64_t off = stage_offset(nx);
             if (uniform) {
 #pragma unroll
                 for (int j = 0; j < kRowsPerLoad; ++j)
@@ -159,7 +159,7 @@ __device__ __forceinline__ void full_blocks_any(uint64_t H[8], uint64_t src, uin
         first = make_uint4(D[32], D[33], D[34], D[35]);
         const uint32_t nx = b + 1;
         if (nx < nmax) {
-            const uint64_t off = (uint64_t)kStageBytes * nx;
+            const uint64_t off = stage_offset(nx);
             if (nx < all) {
 #pragma unroll
                 for (int j = 0; j < kRowsPerLoad; ++j)
