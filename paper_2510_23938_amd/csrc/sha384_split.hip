@@ -319,16 +319,34 @@ __device__ __forceinline__ uint64_t own_part(uint64_t x3, const Half& c, uint64_
     return x + kw;
 }
 
-// x plus the chunk's other lane's y.  A DPP operand may be read no sooner than
-// two instructions after it is written, and the compiler does not see into the
-// block: `fresh` waits that out, elsewhere y is a step old.
-template <bool fresh>
-__device__ __forceinline__ uint64_t add_partner(uint64_t x, uint64_t y) {
+// x plus the chunk's other lane's y, in two halves: the low words' sum leaves
+// its carry in VCC, and the high words' sum takes it from there.  Two things
+// the hardware does not wait for and the compiler, which does not see into the
+// blocks, does not add waits for: VCC may be read by a vector instruction no
+// sooner than two instructions after one wrote it, so the halves have at least
+// two instructions between them, and a DPP operand no sooner than two after it
+// is written (`fresh` waits that out, elsewhere y is a step old).
+// tests/test_isa_waits.py reads both distances in the kernel's code.
+__device__ __forceinline__ uint32_t add_partner_low(uint32_t x, uint32_t y, uint64_t& carry) {
+    uint32_t r;
+    register uint64_t vcc asm("vcc");
+    asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=v"(r), "=s"(vcc) : "v"(y), "v"(x));
+    carry = vcc;
+    return r;
+}
+__device__ __forceinline__ uint32_t add_partner_high(uint32_t x, uint32_t y, uint64_t carry) {
+    uint32_t r;
+    register uint64_t vcc asm("vcc") = carry;  // written too
+    asm("v_addc_co_u32_dpp %0, vcc, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=v"(r), "+s"(vcc) : "v"(y), "v"(x));
+    return r;
+}
+// Both at once, with the waits.
+__device__ __forceinline__ uint64_t add_partner_fresh(uint64_t x, uint64_t y) {
     uint32_t lo, hi;
-    if constexpr (fresh) asm volatile("s_nop 1");
-    HV_PIN;
-    asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+    asm("s_nop 1\n\tv_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_addc_co_u32_dpp %1, vcc, %4, %5, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
         : "=&v"(lo), "=v"(hi) : "v"(lo32(y)), "v"(lo32(x)), "v"(hi32(y)), "v"(hi32(x)) : "vcc");
     return pack(hi, lo);
 }
@@ -338,7 +356,9 @@ __device__ __forceinline__ uint64_t add_partner(uint64_t x, uint64_t y) {
 // -d or h + K + W and the partner's value, formed in the step before; its place
 // is taken by the next step's (word next_kw).  The order is fixed, as in
 // sha256_split.hip, with two or more instructions between any and the one that
-// needs it.
+// needs it, except the last addition's t.  (With the halves of the partner's
+// addition next to each other and t before them, the same time: 9,225 chunks of
+// 256 KiB 5.96 ms, 5.95 in this order.)
 template <int s>
 __device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t& q, uint64_t next_kw) {
     const uint64_t x0 = R[(0 - s) & 3], x1 = R[(1 - s) & 3], x2 = R[(2 - s) & 3];
@@ -349,11 +369,18 @@ __device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t& q, 
     HV_PIN;
     const uint64_t j = rotr64_below_32(x0, c.r2);
     HV_PIN;
-    const uint64_t p = bitop3_64<0x2D>(x0, x1, pack(c.m, c.m));  // a ^ b, or ~e
-    HV_PIN;
     const uint64_t own = n + next_kw;
     HV_PIN;
+    const uint64_t p = bitop3_64<0x2D>(x0, x1, pack(c.m, c.m));  // a ^ b, or ~e
+    HV_PIN;
     const uint64_t y = bitop3_64<0x96>(x0, i, j);
+    HV_PIN;
+    // where a branch follows, the compiler may move what is between the halves
+    // behind it
+    constexpr bool split = s != 63 && s < 80;
+    uint64_t carry = 0;
+    uint32_t low = 0;
+    if constexpr (split) low = add_partner_low(lo32(own), lo32(x0), carry);
     HV_PIN;
     const uint64_t f = bitop3_64<0xCA>(p, x2, x1);  // Maj(a, b, c), or Ch(e, f, g)
     HV_PIN;
@@ -361,7 +388,10 @@ __device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t& q, 
     HV_PIN;
     const uint64_t t = f + q;
     HV_PIN;
-    q = add_partner<false>(own, x0);
+    if constexpr (split)
+        q = pack(add_partner_high(hi32(own), hi32(x0), carry), low);
+    else
+        q = add_partner_fresh(own, x0);
     HV_PIN;
     R[(3 - s) & 3] = sigma + t;
     HV_PIN;
@@ -408,7 +438,7 @@ __device__ __forceinline__ void consume(uint32_t b, uint32_t& slot, uint32_t nma
         for (int e = 0; e < 8; ++e) q[e] = sched[from][8 * j + e][col];
     };
     wait_lds();
-    uint64_t own = add_partner<true>(own_part(R[3], c, pack(cur[0].y, cur[0].x)), R[1]);
+    uint64_t own = add_partner_fresh(own_part(R[3], c, pack(cur[0].y, cur[0].x)), R[1]);
     read(slot, 1, nxt);
     place_code();
     steps<0, 16>(R, H, c, own, cur, nxt);
