@@ -46,12 +46,12 @@ OPS_PER_BLOCK_384 = 80 * 27 + 64 * 19 + 8 + 32
 # that this dual issue allows, beside the one-op-per-lane-cycle peak.
 DUAL_ISSUE_CYCLES = {"sha256": 832 * 4 + 568 * 2, "sha384": 2392 * 4 + 1024 * 2}
 CSRC = "paper_2510_23938_amd/csrc/"
-# per hash: block bytes, length-field bytes, ops per block, leaf kernel, traffic summary, kernel sources
+# per hash: block bytes, length-field bytes, ops per block, traffic summary, sources of the one-wave leaf kernel
 ALGS = {
-    "sha256": (64, 8, OPS_PER_BLOCK, "sha256_leaves_kernel", "sha256_leaves_traffic.json",
-               [CSRC + "sha256_leaves.hip", CSRC + "sha256_device.h"]),
-    "sha384": (128, 16, OPS_PER_BLOCK_384, "sha384_leaves_kernel", "sha384_leaves_traffic.json",
-               [CSRC + "sha384_leaves.hip", CSRC + "sha384_device.h"]),
+    "sha256": (64, 8, OPS_PER_BLOCK, "sha256_leaves_traffic.json",
+               [CSRC + "sha256_leaves.hip", CSRC + "sha256_device.h", CSRC + "stage.h"]),
+    "sha384": (128, 16, OPS_PER_BLOCK_384, "sha384_leaves_traffic.json",
+               [CSRC + "sha384_leaves.hip", CSRC + "sha384_device.h", CSRC + "stage.h"]),
 }
 
 
@@ -61,10 +61,18 @@ def log(*a):
 
 def kernel_source_hash(alg="sha256"):
     h = hashlib.sha256()
-    for p in ALGS[alg][5]:
+    for p in ALGS[alg][4]:
         with open(os.path.join(ROOT, p), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def leaf_kernel_name(alg, launch):
+    """The kernel of a leaf launch (hv.leaf_launch_for)."""
+    if (alg, launch) == ("sha384", "two-wave-compact"):
+        return "sha384_pairs_kernel"
+    return f"{alg}_" + {"one-wave": "leaves", "two-wave": "chain", "two-wave-compact": "chain",
+                        "three-group": "triple", "tape": "tape"}[launch] + "_kernel"
 
 
 def sha_blocks(lens, C, alg="sha256"):
@@ -90,7 +98,7 @@ def traffic_for_current_kernel(alg="sha256", config=5):
     summary, or None when it is missing, covers another workload or was taken
     on different kernel code."""
     try:
-        with open(os.path.join(ROOT, "profiles", ALGS[alg][4])) as f:
+        with open(os.path.join(ROOT, "profiles", ALGS[alg][3])) as f:
             rec = json.load(f)
     except (OSError, ValueError):
         return None
@@ -619,7 +627,7 @@ def main():
     log(f"workload {args.config}: {wl.description}; generated in {time.perf_counter() - t0:.1f} s")
     mode = "manifest" if wl.manifest else "single"
     alg = args.alg
-    block_bytes, _, ops_per_block, leaf_kernel, _, _ = ALGS[alg]
+    block_bytes, _, ops_per_block, _, _ = ALGS[alg]
     pipe = hv.Pipeline(wl.msgs, wl.chunk_bytes, mode, dev, alg=alg)
 
     # the first pass fixes the expected root the timed steps verify against
@@ -692,9 +700,8 @@ def main():
                   "leaf_kernel_median_ms": round(float(np.median(kernel_ms)), 3)}
     blocks = sha_blocks(wl.msgs.lens, wl.chunk_bytes, alg)
     achieved = blocks * ops_per_block / (k_ms / 1e3) / 1e12
-    ran = hv.leaf_kernel_for(pipe.n_leaves)  # the leaf kernel the timed passes ran
-    if ran != "one-wave":
-        leaf_kernel = "sha384_pairs_kernel" if (alg, ran) == ("sha384", "two-wave-compact") else f"{alg}_chain_kernel"
+    ran = hv.leaf_launch_for(len(wl.msgs), pipe.n_leaves, wl.chunk_bytes, alg)  # what the timed passes ran
+    leaf_kernel = leaf_kernel_name(alg, ran)
     log(f"{args.steps} steps: {ms_step:.2f} ms/step, {value:.1f} GB/s (median step {med:.2f} ms, spread "
         f"{step_stats['spread_pct']:.2f}%); leaf kernel {k_ms:.2f} ms avg ({total / k_ms / 1e6:.1f} GB/s, "
         f"{achieved:.2f} TOP/s); prepared pass {prepared_ms:.2f} ms/step")

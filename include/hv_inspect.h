@@ -50,6 +50,18 @@ hv_status hv_set_leaf_kernel(int choice);
  * Errors: HV_ERR_INVALID_ARG for a NULL kernel. */
 hv_status hv_leaf_kernel_for(uint64_t n_leaves, int* kernel);
 
+/* The leaf launch of a hash call or a prepared pass (hv_plan.h) over n_leaves
+ * leaves of n_msgs messages under this thread's choice, on a device of `cus`
+ * compute units, or on the current device when cus = 0, for tests and
+ * measurements: *launch = 1 (one-wave), 2 (two-wave, 64 chunks per workgroup),
+ * 3 (two-wave, 128), 4 (three-group) or 5 (one-wave, the work split evenly over
+ * the resident waves; with a workspace of hv_hash_workspace_bytes).
+ * Host only; with cus > 0 no device is needed.
+ * Errors: HV_ERR_INVALID_ARG for an unknown algorithm or a NULL launch;
+ * HV_ERR_HIP if cus = 0 and the current device cannot be queried. */
+hv_status hv_leaf_launch_for(hv_alg alg, uint32_t n_msgs, uint64_t n_leaves, uint64_t chunk_bytes, uint32_t cus,
+                             int* launch);
+
 /* The launches hv_merkle_reduce_alg makes for these segments on a device of
  * `cus` compute units, or on the current device when cus = 0 (RFC 6962
  * section 2.1's tree, built level by level; Algorithm 1's

@@ -52,20 +52,24 @@ HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves) {
     return L;
 }
 
+int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_leaves, uint32_t cus, uint32_t* waves) {
+    const int k = hv::leaf_launch_for(alg == HV_SHA384 ? hv::kAlgSha384 : hv::kAlgSha256, n_leaves, false, cus);
+    if (k != hv::kLeafOneWave || chunk_bytes == 0 || !tape_worth(n_msgs, n_leaves)) return k;
+    *waves = hv::tape_waves(n_leaves, cus);
+    return *waves > 0 ? hv::kLeafTape : k;
+}
+
 hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,
                          uint64_t n_leaves, uint8_t* digests, hipStream_t stream) {
     const bool sha384 = alg == HV_SHA384;
-    if (tape && chunk_bytes > 0 && tape_worth(n_msgs, n_leaves) && hv::leaf_kernel_for(n_leaves, false) == 1) {
-        hv::Tape t = L.tape;
-        t.waves = hv::tape_waves(n_leaves);
+    hv::Tape t = L.tape;
+    if (tape && leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves) == hv::kLeafTape) {
         t.full_len = sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1;
-        if (t.waves > 0) {
-            const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
-                                                      n_msgs, t, stream);
-            if (e != hipSuccess) return e;
-            return sha384 ? hv::launch_sha384_tape(L.desc, n_leaves, n_leaves, digests, t, stream)
-                          : hv::launch_sha256_tape(L.desc, n_leaves, n_leaves, digests, t, stream);
-        }
+        const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
+                                                  n_msgs, t, stream);
+        if (e != hipSuccess) return e;
+        return sha384 ? hv::launch_sha384_tape(L.desc, n_leaves, n_leaves, digests, t, stream)
+                      : hv::launch_sha256_tape(L.desc, n_leaves, n_leaves, digests, t, stream);
     }
     return sha384 ? hv::launch_sha384_auto(L.desc, n_leaves, n_leaves, digests, stream)
                   : hv::launch_sha256_auto(L.desc, n_leaves, n_leaves, digests, stream);
@@ -730,7 +734,24 @@ hv_status hv_set_leaf_kernel(int choice) {
 
 hv_status hv_leaf_kernel_for(uint64_t n_leaves, int* kernel) {
     if (kernel == nullptr) return fail(HV_ERR_INVALID_ARG, "kernel is NULL");
-    *kernel = hv::leaf_kernel_for(n_leaves, false);
+    // SHA-256's rule; its three-group kernel counts as the one-wave kernel here
+    const int k = hv::leaf_launch_for(hv::kAlgSha256, n_leaves, false, hv::device_cus());
+    *kernel = k == hv::kLeafThreeGroup ? hv::kLeafOneWave : k;
+    return HV_OK;
+}
+
+hv_status hv_leaf_launch_for(hv_alg alg, uint32_t n_msgs, uint64_t n_leaves, uint64_t chunk_bytes, uint32_t cus,
+                             int* launch) {
+    if (alg != HV_SHA256 && alg != HV_SHA384) return fail(HV_ERR_INVALID_ARG, "unknown algorithm %d", (int)alg);
+    if (launch == nullptr) return fail(HV_ERR_INVALID_ARG, "launch is NULL");
+    if (cus == 0) {
+        int dev = -1;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = device_cus(dev, &cus);
+        if (e != hipSuccess) return hip_fail(e, "device query");
+    }
+    uint32_t waves = 0;
+    *launch = leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, cus, &waves);
     return HV_OK;
 }
 

@@ -70,6 +70,11 @@ inline hipError_t upload_messages(hv::MsgDesc* to, const hv_msg* msgs, uint32_t 
                             2 * (size_t)n_msgs, stream);
 }
 
+// What launch_leaves runs for such a table on a device of `cus` compute units
+// under this thread's choice (hv::kLeaf...), with the tape's scratch; for
+// kLeafTape, *waves is the tape's.
+int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_leaves, uint32_t cus, uint32_t* waves);
+
 // The leaf kernel of a scheduled table (L.desc, L.off): the automatic choice,
 // over a tape where `tape` (L's tape scratch is there) and it pays.
 hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,

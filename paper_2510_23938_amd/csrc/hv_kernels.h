@@ -86,8 +86,9 @@ hipError_t launch_sha256_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t o
 hipError_t launch_sha384_tape(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               const Tape& t, hipStream_t s);
 // Waves of the tape that a one-wave call over n_slots leaves, nearly all of
-// them full chunks, is cut into; 0 where the plain launch is as fast.
-uint32_t tape_waves(uint64_t n_slots);
+// them full chunks, is cut into on a device of `cus` compute units; 0 where the
+// plain launch is as fast.
+uint32_t tape_waves(uint64_t n_slots, uint32_t cus);
 
 // SHA-384 of the n_slots leaves of a leaf table (sha384_leaves.hip): 48-byte
 // digests at digests + 48 * desc.out for desc.out < out_bound.
@@ -125,10 +126,17 @@ hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t 
 // by the same rules as launch_sha256_auto.
 hipError_t launch_sha384_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background = false);
-// The leaf kernel a call over n_slots leaves takes under this thread's choice
-// on the current device: 1 one-wave, 2 two-wave with 64 chunks per workgroup,
-// 3 two-wave with 128 (both hashes use this rule).
-int leaf_kernel_for(uint64_t n_slots, bool background);
+// What a leaf launch runs (hv_leaf_launch_for's values).
+enum : int {
+    kLeafOneWave = 1,
+    kLeafTwoWave = 2,         // 64 chunks per workgroup
+    kLeafTwoWaveCompact = 3,  // 128
+    kLeafThreeGroup = 4,      // SHA-256 only
+    kLeafTape = 5,            // one-wave over a tape (Tape)
+};
+// The kernel a launch over n_slots leaves takes under this thread's choice on
+// a device of `cus` compute units, where it has no tape.
+int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus);
 // Compute units of the current device (queried once per device; 0 if the
 // query fails, which makes the automatic choices take the one-wave kernels).
 uint32_t device_cus();

@@ -611,27 +611,32 @@ uint32_t device_cus() {
     return (uint32_t)n;
 }
 
-int leaf_kernel_for(uint64_t n_slots, bool background) {
+int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus) {
     const int choice = leaf_kernel_choice();
-    const uint64_t cus = device_cus();
     // the two-wave kernels while every CU holds one workgroup at most: 64
     // KiB chunks take 1.18 ms up to 64 per CU and 1.60 up to 128, against 2.69
     // with the one-wave kernel; with more, two workgroups share a CU and the
-    // one-wave kernel (or SHA-256's three-group one, launch_sha256_auto) is
+    // one-wave kernel (or SHA-256's three-group one) is
     // faster.  Background work keeps the one-wave kernel:
     // shorter chains cost more instructions, about 1.4x the CU time per byte.
-    if (choice == 1 || (choice == 0 && (background || n_slots > 128 * cus))) return 1;
-    return choice == 3 || n_slots > 64 * cus ? 3 : 2;
+    if (choice == 1 || (choice == 0 && (background || n_slots > 128 * cus))) {
+        // SHA-256, up to three groups per CU, one workgroup each: 2.07 ms
+        // against 2.72 for 64 KiB chunks (above kSent); with more, the one-wave
+        // kernel has a wave for every SIMD
+        const bool three = alg == kAlgSha256 && choice == 0 && !background && n_slots <= 64 * kTriple * cus;
+        return three ? kLeafThreeGroup : kLeafOneWave;
+    }
+    return choice == 3 || n_slots > 64 * cus ? kLeafTwoWaveCompact : kLeafTwoWave;
 }
 
-uint32_t tape_waves(uint64_t n_slots) {
+uint32_t tape_waves(uint64_t n_slots, uint32_t cus) {
     // In units of a wave's time when a SIMD is full: one wave alone on a SIMD
     // takes 1.10 (64 KiB chunks: 2.72 ms), two 2.04 (5.06), three 3 (7.44), and
     // a fourth waits for one of them.  x waves per SIMD run plainly as threes
     // and a remainder; on a tape, as w at once (at most x: an interval is no
     // shorter than a chunk), each x / w long.
     static constexpr double kAtOnce[4] = {0, 1.10, 2.04, 3.0};
-    const uint32_t simds = 4 * device_cus();
+    const uint32_t simds = 4 * cus;
     if (simds == 0 || 3 * simds > kTapeMaxWaves) return 0;
     const double x = (double)n_slots / 64 / simds;
     const uint64_t whole = (n_slots + 64 * (uint64_t)simds - 1) / (64 * (uint64_t)simds);
@@ -647,19 +652,14 @@ uint32_t tape_waves(uint64_t n_slots) {
 
 hipError_t launch_sha256_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background) {
-    const int k = leaf_kernel_for(n_slots, background);
-    if (k == 1) {
-        // up to three groups per CU, one workgroup each: 2.07 ms against 2.72
-        // for 64 KiB chunks (above kSent); with more, the one-wave kernel has a
-        // wave for every SIMD.  Background work as above.
-        if (leaf_kernel_choice() == 0 && !background && n_slots <= 64 * kTriple * (uint64_t)device_cus()) {
-            sha256_triple_kernel<<<(unsigned)((n_slots + 64 * kTriple - 1) / (64 * kTriple)), 512, 0, s>>>(
-                desc, n_slots, out_bound, digests);
-            return hipGetLastError();
-        }
-        return launch_sha256_leaves(desc, n_slots, out_bound, digests, s);
+    const int k = leaf_launch_for(kAlgSha256, n_slots, background, device_cus());
+    if (k == kLeafThreeGroup) {
+        sha256_triple_kernel<<<(unsigned)((n_slots + 64 * kTriple - 1) / (64 * kTriple)), 512, 0, s>>>(
+            desc, n_slots, out_bound, digests);
+        return hipGetLastError();
     }
-    return launch_sha256_split(desc, n_slots, out_bound, digests, k == 3, s);
+    if (k == kLeafOneWave) return launch_sha256_leaves(desc, n_slots, out_bound, digests, s);
+    return launch_sha256_split(desc, n_slots, out_bound, digests, k == kLeafTwoWaveCompact, s);
 }
 
 hipError_t launch_sha256_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,

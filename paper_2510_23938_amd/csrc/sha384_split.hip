@@ -552,9 +552,9 @@ __global__ void __launch_bounds__(256) sha384_chain_kernel(const LeafDesc* __res
 
 hipError_t launch_sha384_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background) {
-    const int k = leaf_kernel_for(n_slots, background);  // the same rule as SHA-256's
-    if (k == 1) return launch_sha384_leaves(desc, n_slots, out_bound, digests, s);
-    return launch_sha384_split(desc, n_slots, out_bound, digests, k == 3, s);
+    const int k = leaf_launch_for(kAlgSha384, n_slots, background, device_cus());
+    if (k == kLeafOneWave) return launch_sha384_leaves(desc, n_slots, out_bound, digests, s);
+    return launch_sha384_split(desc, n_slots, out_bound, digests, k == kLeafTwoWaveCompact, s);
 }
 
 hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,

@@ -49,7 +49,8 @@ EXPORTS = (
     "hv_merkle_reduce", "hv_verify_workspace_bytes", "hv_verify_root", "hv_compare_roots",
     "hv_hash_chunks_alg", "hv_merkle_workspace_bytes_alg", "hv_merkle_reduce_alg", "hv_verify_root_alg",
     "hv_compare_roots_alg", "hv_hash_chunks_noalloc", "hv_last_error", "hv_set_kernel_timing", "hv_leaf_kernel_ms",
-    "hv_leaf_schedule", "hv_set_leaf_kernel", "hv_leaf_kernel_for", "hv_merkle_launches",  # include/hv_inspect.h
+    "hv_leaf_schedule", "hv_set_leaf_kernel", "hv_leaf_kernel_for", "hv_leaf_launch_for",
+    "hv_merkle_launches",  # include/hv_inspect.h
     "hv_mb_valu", "hv_mb_sha256", "hv_mb_valu64", "hv_mb_sha384", "hv_mb_op_rate",
     "hv_mb_hbm_read",  # include/hv_microbench.h
     "hv_stream_workspace_bytes", "hv_hash_host_chunks", "hv_hash_host_chunks_alg",  # include/hv_stream.h
@@ -127,6 +128,7 @@ def _load():
         "hv_leaf_schedule": ([vp, u32, u64, vp, vp, sz, vp], ctypes.c_int),
         "hv_set_leaf_kernel": ([ctypes.c_int], ctypes.c_int),
         "hv_leaf_kernel_for": ([ctypes.c_uint64, ctypes.c_void_p], ctypes.c_int),
+        "hv_leaf_launch_for": ([ctypes.c_int32, u32, u64, u64, u32, vp], ctypes.c_int),
         "hv_merkle_launches": ([ctypes.c_int32, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_void_p,
                                 ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int),
         "hv_mb_valu": ([vp, u32, u32, vp, vp], ctypes.c_int),
@@ -603,6 +605,16 @@ def leaf_kernel_for(n_leaves: int) -> str:
     k = ctypes.c_int(0)
     _check(lib.hv_leaf_kernel_for(int(n_leaves), ctypes.byref(k)))
     return {1: "one-wave", 2: "two-wave", 3: "two-wave-compact"}[k.value]
+
+
+def leaf_launch_for(n_msgs: int, n_leaves: int, chunk_bytes: int, alg: str = "sha256", cus: int = 0) -> str:
+    """The leaf launch of a hash call or prepared pass over n_leaves leaves of n_msgs messages, on a device of
+    ``cus`` compute units (0: the current device) under this thread's choice: "one-wave", "two-wave",
+    "two-wave-compact", "three-group" or "tape" (one-wave, split evenly over the resident waves)."""
+    code, _ = _alg(alg)
+    k = ctypes.c_int(0)
+    _check(lib.hv_leaf_launch_for(code, int(n_msgs), int(n_leaves), int(chunk_bytes), int(cus), ctypes.byref(k)))
+    return {1: "one-wave", 2: "two-wave", 3: "two-wave-compact", 4: "three-group", 5: "tape"}[k.value]
 
 
 def merkle_launches(seg_offsets, alg: str = "sha256", cus: int = 0) -> list:

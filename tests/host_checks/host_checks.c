@@ -282,6 +282,10 @@ static void rejections(void) {
     REJECTED(hv_set_leaf_kernel(-1), HV_ERR_INVALID_ARG);
     REJECTED(hv_set_leaf_kernel(4), HV_ERR_INVALID_ARG);
     CHECK(hv_set_leaf_kernel(0) == HV_OK);
+    int launch = 0;
+    REJECTED(hv_leaf_launch_for(9, 1, 10, 4096, 256, &launch), HV_ERR_INVALID_ARG);
+    REJECTED(hv_leaf_launch_for(HV_SHA256, 1, 10, 4096, 256, NULL), HV_ERR_INVALID_ARG);
+    CHECK(hv_leaf_launch_for(HV_SHA256, 1, 10, 4096, 256, &launch) == HV_OK && launch == 2);
     float ms = 0;
     REJECTED(hv_leaf_kernel_ms(NULL), HV_ERR_INVALID_ARG);
     REJECTED(hv_leaf_kernel_ms(&ms), HV_ERR_INVALID_ARG); /* nothing was timed on this thread */
