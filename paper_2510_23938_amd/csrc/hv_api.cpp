@@ -54,7 +54,8 @@ HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves) {
 
 int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_leaves, uint32_t cus, uint32_t* waves) {
     const int k = hv::leaf_launch_for(alg == HV_SHA384 ? hv::kAlgSha384 : hv::kAlgSha256, n_leaves, false, cus);
-    if (k != hv::kLeafOneWave || chunk_bytes == 0 || !tape_worth(n_msgs, n_leaves)) return k;
+    if (k != hv::kLeafOneWave || hv::leaf_kernel_choice() != 0 || chunk_bytes == 0 || !tape_worth(n_msgs, n_leaves))
+        return k;
     *waves = hv::tape_waves(n_leaves, cus);
     return *waves > 0 ? hv::kLeafTape : k;
 }

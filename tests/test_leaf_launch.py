@@ -34,6 +34,15 @@ def test_rule_by_leaf_count():
         assert launch(256 * CU + 1, alg, msgs=20000) == "one-wave"  # many tails
 
 
+def test_a_forced_choice_runs_the_kernel_it_names():
+    for n in (100, 128 * CU + 1, 256 * CU + 1, 512 * CU + 64):
+        for name in ("one-wave", "two-wave-compact"):
+            hv.set_leaf_kernel(name)
+            assert launch(n) == launch(n, "sha384") == name
+    hv.set_leaf_kernel("two-wave")
+    assert [launch(n) for n in (64 * CU, 64 * CU + 1)] == ["two-wave", "two-wave-compact"]
+
+
 def test_other_devices():
     assert hv.leaf_launch_for(1, 100 * 100, 65536, cus=100) == "two-wave-compact"
     # the tape's scratch is for up to 256 CUs
