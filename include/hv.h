@@ -107,7 +107,7 @@ hv_status hv_pack_messages(const uint64_t* data, const uint64_t* nbytes, uint32_
 
 /* Workspace bytes hv_hash_chunks needs for n_msgs messages with n_leaves
  * leaves in total (from hv_leaf_layout); 0 (and hv_last_error set) for more
- * than 2^31 leaves.  For 65537 to 2^20 leaves of at most a quarter as many
+ * than 2^31 leaves.  For 65537 to 2^19 leaves of at most a quarter as many
  * messages it counts 12 MiB with which the work is split evenly over the chip;
  * the call also takes a workspace without them and then runs a little longer. */
 size_t hv_hash_workspace_bytes(uint32_t n_msgs, uint64_t n_leaves);

@@ -7,7 +7,7 @@
 // SHA-384 13.3 and 10.1; 66,000 chunks: 5.1 and 2.8 ms).  A chunk is a chain,
 // but a chain can be cut: its state after some block is 32 or 64 bytes, and
 // another wave can go on from it.  So the table's groups of 64 slots are laid
-// end to end on a tape (a group's length: its most blocks), the tape is cut
+// end to end on a tape (a group's length: its set-up and its most blocks), the tape is cut
 // into one equal interval per resident wave, and a group across a boundary is
 // shared by the two intervals (the wrap-around rule of preemptive scheduling
 // on identical machines, McNaughton 1959): the interval on the right hashes
@@ -34,19 +34,21 @@ constexpr uint64_t kStateBytes = kTapeStateBytes;  // 64 lanes of at most eight 
 struct Piece {
     uint64_t group;
     uint32_t from, to;  // from > 0: go on from the states of the wave before
-    bool last;          // to is the group's end (padding included)
+    bool last;          // to is the group's end (padding included); else, to is 0
+                        // where only set-up lies in this interval: nothing to do
 };
 
 // The intervals of a tape, walked by one wave: all values are wave-uniform.
 struct TapeWalk {
     const uint64_t* tail_start;  // tape position of each group with a tail, and the tape's end
     uint64_t full_groups;        // the groups of full chunks only, the table's first
-    uint64_t full_len;           // blocks of each of them
+    uint64_t full_len;           // length of each of them
+    uint32_t setup;              // of a group's length, before its blocks
     uint64_t group, start;       // the group `pos` lies in, and its tape position
     uint64_t pos, end;           // what is left of the interval
 
-    __device__ __forceinline__ TapeWalk(const Tape& t, uint64_t n_slots, uint32_t wave)
-        : tail_start(t.head + 1), full_groups(t.head[0]), full_len(t.full_len) {
+    __host__ __device__ __forceinline__ TapeWalk(const Tape& t, uint64_t n_slots, uint32_t wave)
+        : tail_start(t.head + 1), full_groups(t.head[0]), full_len(t.full_len), setup(t.setup) {
         const uint32_t tail_groups = (uint32_t)((n_slots + 63) / 64 - full_groups);
         const uint64_t total = tail_start[tail_groups];
         uint64_t share = (total + t.waves - 1) / t.waves;
@@ -71,7 +73,7 @@ struct TapeWalk {
         }
     }
 
-    __device__ __forceinline__ bool next(Piece* p) {
+    __host__ __device__ __forceinline__ bool next(Piece* p) {
         if (pos >= end) return false;
         const uint64_t len =
             group < full_groups ? full_len : tail_start[group - full_groups + 1] - tail_start[group - full_groups];
@@ -80,8 +82,9 @@ struct TapeWalk {
         p->group = group;
         // at the interval's start the group's first blocks; at its end the last ones
         p->last = left == 0;
-        p->from = p->last ? (uint32_t)(len - here) : 0u;
-        p->to = p->from + (uint32_t)here;
+        const uint32_t from = p->last ? (uint32_t)(len - here) : 0u, to = from + (uint32_t)here;
+        p->from = from > setup ? from - setup : 0u;
+        p->to = to > setup ? to - setup : 0u;
         pos += here;
         start += len;
         ++group;

@@ -54,7 +54,8 @@ HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves) {
 
 int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_leaves, uint32_t cus, uint32_t* waves) {
     const int k = hv::leaf_launch_for(alg == HV_SHA384 ? hv::kAlgSha384 : hv::kAlgSha256, n_leaves, false, cus);
-    if (k != hv::kLeafOneWave || hv::leaf_kernel_choice() != 0 || chunk_bytes == 0 || !tape_worth(n_msgs, n_leaves))
+    if (k != hv::kLeafOneWave || hv::leaf_kernel_choice() != 0 || !tape_worth(n_msgs, n_leaves) ||
+        !tape_chunks(n_msgs, n_leaves, chunk_bytes))
         return k;
     *waves = hv::tape_waves(n_leaves, cus);
     return *waves > 0 ? hv::kLeafTape : k;
@@ -65,7 +66,8 @@ hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_
     const bool sha384 = alg == HV_SHA384;
     hv::Tape t = L.tape;
     if (tape && leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves) == hv::kLeafTape) {
-        t.full_len = sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1;
+        t.setup = sha384 ? hv::kTapeSetup384 : hv::kTapeSetup256;
+        t.full_len = (sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1) + t.setup;
         const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
                                                   n_msgs, t, stream);
         if (e != hipSuccess) return e;

@@ -54,13 +54,22 @@ struct HashLayout {
 HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves);
 
 // Calls for which the leaf table's work may be split evenly over the resident
-// waves (balance.h): more than one wave per SIMD (256 CUs), up to 16 (beyond
-// that a partly filled last round is at most a few percent, and the scratch
-// would not fit beside the table in hv_hash_chunks_noalloc's array), and few
-// messages per leaf, so that nearly all chunks are full ones when the call
-// has a chunk size at all.
+// waves (balance.h), and which have scratch for it: more than one wave per SIMD
+// (256 CUs), up to 8 (beyond that a partly filled last round is a few percent,
+// no more than the walk costs: 700,000 and 10^6 chunks took 0.98 to 1.00 of the
+// plain launch's rate), and few messages per leaf, so that nearly all chunks are
+// full ones when the call has a chunk size at all.
 inline bool tape_worth(uint32_t n_msgs, uint64_t n_leaves) {
-    return n_leaves > 65536 && n_leaves <= (1u << 20) && n_msgs <= n_leaves / 4;
+    return n_leaves > 65536 && n_leaves <= (1u << 19) && n_msgs <= n_leaves / 4;
+}
+// Of those, the calls whose chunks are long enough: a tape has three waves on a
+// SIMD where the plain launch has four and more for chunks of a few blocks, and
+// its plan is a launch of its own.  Tape against plain: 1 KiB chunks 0.8 to 1.1
+// from 115,000 leaves on (512-byte ones 0.65 to 0.8), 2 KiB 1.0 to 1.5 where few
+// are tails and 0.86 to 1.3 where a seventh are, 4 KiB 0.96 to 1.6, 64 KiB 1.0 to
+// 1.8.
+inline bool tape_chunks(uint32_t n_msgs, uint64_t n_leaves, uint64_t chunk_bytes) {
+    return chunk_bytes >= 4096 || (chunk_bytes >= 2048 && n_msgs <= n_leaves / 16);
 }
 
 // A message table to the device; `msgs` is read before the call returns.

@@ -309,12 +309,12 @@ __global__ void __launch_bounds__(kThreads) tape_plan_kernel(const LeafDesc* __r
     const uint64_t lo = threadIdx.x * per < tails ? threadIdx.x * per : tails;
     const uint64_t hi = lo + per < tails ? lo + per : tails;
     uint64_t s = 0;
-    for (uint64_t i = lo; i < hi; ++i) s += class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
+    for (uint64_t i = lo; i < hi; ++i) s += t.setup + class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
     Pair sum;
     uint64_t at = full * t.full_len + block_exclusive_scan(make_ulonglong2(s, 0), &sum).x;
     for (uint64_t i = lo; i < hi; ++i) {
         t.head[1 + i] = at;
-        at += class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
+        at += t.setup + class_blocks(desc[64 * (full + i)].nbytes, block_bytes, pad);
     }
     if (threadIdx.x == 0) {
         t.head[0] = full;

@@ -632,7 +632,8 @@ int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus) {
 uint32_t tape_waves(uint64_t n_slots, uint32_t cus) {
     // In units of a wave's time when a SIMD is full: one wave alone on a SIMD
     // takes 1.10 (64 KiB chunks: 2.72 ms), two 2.04 (5.06), three 3 (7.44), and
-    // a fourth waits for one of them.  x waves per SIMD run plainly as threes
+    // a fourth waits for one of them (SHA-384: 3.51, 6.35 and 9.30 ms, 1.13, 2.05
+    // and 3; nearly the same choices).  x waves per SIMD run plainly as threes
     // and a remainder; on a tape, as w at once (at most x: an interval is no
     // shorter than a chunk), each x / w long.
     static constexpr double kAtOnce[4] = {0, 1.10, 2.04, 3.0};
@@ -640,7 +641,7 @@ uint32_t tape_waves(uint64_t n_slots, uint32_t cus) {
     if (simds == 0 || 3 * simds > kTapeMaxWaves) return 0;
     const double x = (double)n_slots / 64 / simds;
     const uint64_t whole = (n_slots + 64 * (uint64_t)simds - 1) / (64 * (uint64_t)simds);
-    double best = ((double)(whole / 3 * 3) + kAtOnce[whole % 3]) * 0.985;  // the walk's own cost
+    double best = ((double)(whole / 3 * 3) + kAtOnce[whole % 3]) * 0.96;  // the walk's own cost
     uint32_t waves = 0;
     for (uint32_t w = 1; w <= 3 && w <= x; ++w)
         if (x / w * kAtOnce[w] < best) {

@@ -251,6 +251,7 @@ __global__ void __launch_bounds__(kThreads, 3) sha384_tape_kernel(const LeafDesc
     TapeWalk walk(tape, n_slots, wave);
     Piece piece;
     while (walk.next(&piece)) {
+        if (!piece.last && piece.to == 0) continue;  // as in the SHA-256 kernel
         const uint64_t slot = 64 * piece.group + (threadIdx.x & 63);
         LeafDesc d = {0, 0, 0};
         if (slot < n_slots) d = desc[slot];

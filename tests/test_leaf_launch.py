@@ -34,6 +34,16 @@ def test_rule_by_leaf_count():
         assert launch(256 * CU + 1, alg, msgs=20000) == "one-wave"  # many tails
 
 
+def test_short_chunks_and_many_leaves_keep_the_plain_launch():
+    # the tape lost there: three waves on a SIMD, and a launch for its plan
+    for alg in ("sha256", "sha384"):
+        for n in (256 * CU + 1, 135000, 300000):
+            assert [launch(n, alg, C=C) for C in (128, 512, 1024, 1920)] == ["one-wave"] * 4
+            assert [launch(n, alg, C=C) for C in (2048, 4096, 16384)] == ["tape"] * 3
+            assert [launch(n, alg, msgs=n // 8, C=C) for C in (2048, 4096)] == ["one-wave", "tape"]
+        assert [launch(n, alg, C=4096) for n in (450000, 520000, 700000, 1000000)] == ["one-wave"] * 4
+
+
 def test_a_forced_choice_runs_the_kernel_it_names():
     for n in (100, 128 * CU + 1, 256 * CU + 1, 512 * CU + 64):
         for name in ("one-wave", "two-wave-compact"):
