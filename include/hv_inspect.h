@@ -65,6 +65,12 @@ hv_status hv_leaf_kernel_for(uint64_t n_leaves, int* kernel);
 hv_status hv_leaf_launch_for(hv_alg alg, uint32_t n_msgs, uint64_t n_leaves, uint64_t chunk_bytes, uint32_t cus,
                              int* launch);
 
+/* How often a wave looks for the chunk states of the wave it shares chunks with
+ * before it hashes those chunks from their first block itself (launch 5 of
+ * hv_leaf_launch_for), per calling thread: at least `polls` times (16384 is
+ * the default), or never with 0.  For tests; the digests do not depend on it. */
+hv_status hv_set_handover_polls(uint32_t polls);
+
 /* The launches hv_merkle_reduce_alg makes for these segments on a device of
  * `cus` compute units, or on the current device when cus = 0 (RFC 6962
  * section 2.1's tree, built level by level; Algorithm 1's

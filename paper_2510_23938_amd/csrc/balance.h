@@ -19,7 +19,7 @@
 // Wave k takes the k-th interval from the right, so a wave only ever waits
 // for the wave before it, which was dispatched no later.  The wait is bounded
 // all the same: a wave that does not see the states in time hashes the group
-// from its first block, with the same result.
+// from its first block, with the same result (load_states).
 #pragma once
 #include <stdint.h>
 #include <hip/hip_runtime.h>
@@ -103,11 +103,15 @@ __device__ __forceinline__ void save_states(const Tape& t, uint32_t wave, const 
         __hip_atomic_store(t.ready + wave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The states the wave before saved; false when they do not come in time.
+// The states after `blocks` blocks that the wave before saved; false when they
+// do not come in time: t.polls looks, 0.4 us apart and more, or for long chunks
+// as many as there are blocks, which is still less than the time they take to
+// hash again (2.6 us each and more).
 template <int NW>
-__device__ __forceinline__ bool load_states(const Tape& t, uint32_t wave, uint32_t* s) {
+__device__ __forceinline__ bool load_states(const Tape& t, uint32_t wave, uint32_t blocks, uint32_t* s) {
+    const uint32_t polls = t.polls == 0 || t.polls > blocks ? t.polls : blocks;
     bool there = false;
-    for (int tries = 0; tries < 1 << 14 && !there; ++tries) {
+    for (uint32_t tries = 0; tries < polls && !there; ++tries) {
         there = __builtin_amdgcn_readfirstlane(
                     __hip_atomic_load(t.ready + (wave - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
         if (!there) __builtin_amdgcn_s_sleep(16);

@@ -61,11 +61,16 @@ int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_le
     return *waves > 0 ? hv::kLeafTape : k;
 }
 
+namespace {
+thread_local uint32_t g_tape_polls = hv::kTapePolls;
+}  // namespace
+
 hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_msgs, uint64_t chunk_bytes,
                          uint64_t n_leaves, uint8_t* digests, hipStream_t stream) {
     const bool sha384 = alg == HV_SHA384;
     hv::Tape t = L.tape;
     if (tape && leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves) == hv::kLeafTape) {
+        t.polls = g_tape_polls;
         t.setup = sha384 ? hv::kTapeSetup384 : hv::kTapeSetup256;
         t.full_len = (sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1) + t.setup;
         const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
@@ -755,6 +760,11 @@ hv_status hv_leaf_launch_for(hv_alg alg, uint32_t n_msgs, uint64_t n_leaves, uin
     }
     uint32_t waves = 0;
     *launch = leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, cus, &waves);
+    return HV_OK;
+}
+
+hv_status hv_set_handover_polls(uint32_t polls) {
+    g_tape_polls = polls;
     return HV_OK;
 }
 

@@ -35,6 +35,7 @@ struct Tape {
     uint64_t full_len;  // length on the tape of a group of full chunks
     uint32_t setup;     // part of every group's length before its blocks
     uint32_t waves;     // a multiple of 4
+    uint32_t polls;     // looks for the states of the wave before, at least; 0: none
 };
 // What a group costs a wave besides its blocks, in blocks: its descriptors, the
 // first stage's loads, the final block and the digests take some 7 us (SHA-256)
@@ -45,6 +46,7 @@ struct Tape {
 // Where nearly all chunks are whole ones they change nothing (205,697 of 64 KiB:
 // 7.81 ms without, 7.83 with them).
 constexpr uint32_t kTapeSetup256 = 3, kTapeSetup384 = 2;
+constexpr uint32_t kTapePolls = 1 << 14;
 constexpr uint64_t kTapeStateBytes = 64 * 64;
 constexpr uint32_t kTapeMaxWaves = 3 * 1024;  // three per SIMD of 256 CUs
 

@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(kThreads, 3) sha384_tape_kernel(const LeafDesc
         if (slot < n_slots) d = desc[slot];
         uint64_t H[8];
         uint32_t words[16];
-        if (piece.from > 0 && !load_states<16>(tape, wave, words)) piece.from = 0;
+        if (piece.from > 0 && !load_states<16>(tape, wave, piece.from, words)) piece.from = 0;
         if (piece.from == 0) {
             init_state384(H);
         } else {

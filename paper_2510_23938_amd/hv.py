@@ -49,7 +49,7 @@ EXPORTS = (
     "hv_merkle_reduce", "hv_verify_workspace_bytes", "hv_verify_root", "hv_compare_roots",
     "hv_hash_chunks_alg", "hv_merkle_workspace_bytes_alg", "hv_merkle_reduce_alg", "hv_verify_root_alg",
     "hv_compare_roots_alg", "hv_hash_chunks_noalloc", "hv_last_error", "hv_set_kernel_timing", "hv_leaf_kernel_ms",
-    "hv_leaf_schedule", "hv_set_leaf_kernel", "hv_leaf_kernel_for", "hv_leaf_launch_for",
+    "hv_leaf_schedule", "hv_set_leaf_kernel", "hv_leaf_kernel_for", "hv_leaf_launch_for", "hv_set_handover_polls",
     "hv_merkle_launches",  # include/hv_inspect.h
     "hv_mb_valu", "hv_mb_sha256", "hv_mb_valu64", "hv_mb_sha384", "hv_mb_op_rate",
     "hv_mb_hbm_read",  # include/hv_microbench.h
@@ -129,6 +129,7 @@ def _load():
         "hv_set_leaf_kernel": ([ctypes.c_int], ctypes.c_int),
         "hv_leaf_kernel_for": ([ctypes.c_uint64, ctypes.c_void_p], ctypes.c_int),
         "hv_leaf_launch_for": ([ctypes.c_int32, u32, u64, u64, u32, vp], ctypes.c_int),
+        "hv_set_handover_polls": ([u32], ctypes.c_int),
         "hv_merkle_launches": ([ctypes.c_int32, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_void_p,
                                 ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int),
         "hv_mb_valu": ([vp, u32, u32, vp, vp], ctypes.c_int),

@@ -80,6 +80,25 @@ def test_long_chunks_and_inexact_classes(alg):
         assert got[8 * whole + i].tobytes() == H(host[:int(t)]).digest()
 
 
+@pytest.mark.parametrize("alg", ["sha256", "sha384"])
+def test_a_wave_that_gives_up_hashes_the_chunks_itself(alg):
+    # no look for the other wave's states: every cut group is hashed from its
+    # first block by the wave that ends it
+    n, C = 65536 + 700, 4096
+    assert hv.leaf_launch_for(1, n, C, alg) == "tape"
+    buf = W.random_bytes(n * C - 77, 10, DEV)
+    msgs = (np.array([buf.data_ptr() + 1], dtype=np.uint64), np.array([n * C - 78], dtype=np.uint64))
+    want, _ = hv.hv_hash_chunks(msgs, C, alg=alg)
+    assert want.cpu().numpy().tobytes() == expected(buf.cpu().numpy(), [1], [n * C - 78], C, alg)
+    hv.lib.hv_set_handover_polls(0)
+    try:
+        got, _ = hv.hv_hash_chunks(msgs, C, out=torch.zeros_like(want), alg=alg)
+        torch.cuda.synchronize()
+    finally:
+        hv.lib.hv_set_handover_polls(1 << 14)
+    assert torch.equal(got, want)
+
+
 def test_workspace_without_tape_and_repeated_runs():
     n, C = 70000, 256
     buf = W.random_bytes(n * C - 5, 9, DEV)
