@@ -35,7 +35,7 @@ struct Piece {
     uint64_t group;
     uint32_t from, to;  // from > 0: go on from the states of the wave before
     bool last;          // to is the group's end (padding included); else, to is 0
-                        // where only set-up lies in this interval: nothing to do
+                        // where only set-up lies in this interval
 };
 
 // The intervals of a tape, walked by one wave: all values are wave-uniform.
@@ -103,15 +103,12 @@ __device__ __forceinline__ void save_states(const Tape& t, uint32_t wave, const 
         __hip_atomic_store(t.ready + wave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The states after `blocks` blocks that the wave before saved; false when they
-// do not come in time: t.polls looks, 0.4 us apart and more, or for long chunks
-// as many as there are blocks, which is still less than the time they take to
-// hash again (2.6 us each and more).
+// The states the wave before saved; false when they do not come in time: after
+// t.polls looks, 0.4 us apart and more.
 template <int NW>
-__device__ __forceinline__ bool load_states(const Tape& t, uint32_t wave, uint32_t blocks, uint32_t* s) {
-    const uint32_t polls = t.polls == 0 || t.polls > blocks ? t.polls : blocks;
+__device__ __forceinline__ bool load_states(const Tape& t, uint32_t wave, uint32_t* s) {
     bool there = false;
-    for (uint32_t tries = 0; tries < polls && !there; ++tries) {
+    for (uint32_t tries = 0; tries < t.polls && !there; ++tries) {
         there = __builtin_amdgcn_readfirstlane(
                     __hip_atomic_load(t.ready + (wave - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
         if (!there) __builtin_amdgcn_s_sleep(16);

@@ -70,9 +70,9 @@ hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_
     const bool sha384 = alg == HV_SHA384;
     hv::Tape t = L.tape;
     if (tape && leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves) == hv::kLeafTape) {
-        t.polls = g_tape_polls;
         t.setup = sha384 ? hv::kTapeSetup384 : hv::kTapeSetup256;
         t.full_len = (sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1) + t.setup;
+        t.polls = g_tape_polls == 0 || t.full_len < g_tape_polls ? g_tape_polls : (uint32_t)t.full_len;
         const hipError_t e = hv::launch_tape_plan(sha384 ? hv::kAlgSha384 : hv::kAlgSha256, L.desc, n_leaves, L.off,
                                                   n_msgs, t, stream);
         if (e != hipSuccess) return e;

@@ -310,10 +310,9 @@ __global__ void __launch_bounds__(kThreads, 3) sha256_tape_kernel(const LeafDesc
     TapeWalk walk(tape, n_slots, wave);
     Piece piece;
     while (walk.next(&piece)) {
-        if (!piece.last && piece.to == 0) continue;  // none of its blocks: the next wave hashes it whole
         uint32_t lane = threadIdx.x & 63;
         uint32_t H[8];
-        if (piece.from > 0 && !load_states<8>(tape, wave, piece.from, H)) piece.from = 0;
+        if (piece.from > 0 && !load_states<8>(tape, wave, H)) piece.from = 0;
         if (piece.from == 0) init_state(H);
         whole_blocks(H, load_desc(desc, 64 * piece.group + lane, n_slots), piece.from, piece.to, piece.last,
                      stage[in_block]);

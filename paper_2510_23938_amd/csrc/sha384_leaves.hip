@@ -251,13 +251,12 @@ __global__ void __launch_bounds__(kThreads, 3) sha384_tape_kernel(const LeafDesc
     TapeWalk walk(tape, n_slots, wave);
     Piece piece;
     while (walk.next(&piece)) {
-        if (!piece.last && piece.to == 0) continue;  // as in the SHA-256 kernel
         const uint64_t slot = 64 * piece.group + (threadIdx.x & 63);
         LeafDesc d = {0, 0, 0};
         if (slot < n_slots) d = desc[slot];
         uint64_t H[8];
         uint32_t words[16];
-        if (piece.from > 0 && !load_states<16>(tape, wave, piece.from, words)) piece.from = 0;
+        if (piece.from > 0 && !load_states<16>(tape, wave, words)) piece.from = 0;
         if (piece.from == 0) {
             init_state384(H);
         } else {
