@@ -1,12 +1,14 @@
 """The one-wave leaf kernels over a tape: the leaf table's work cut into one
 equal interval per resident wave, chunks across a boundary hashed by two waves.
 
-Leaf counts just above one, two and three waves per SIMD, where an interval is
-about one chunk long and every chunk is cut, and counts whose last group is
-partly filled; tails from none to one leaf in four, tails of every length below
+Leaf counts just above one, two, three and four waves per SIMD, where an
+interval is about one chunk long and every chunk is cut, and counts whose last
+group is partly filled; tails from none to one leaf in four (and to more than
+256 groups of them, several per thread of the plan), tails of every length below
 a chunk, and chunks at and above the block count (2048) where the scheduler's
-classes stop being exact, so that a group's tape length is only a bound.
-Digests are bytes, compared with hashlib's for every leaf.
+classes stop being exact, so that a group's tape length is only a bound.  Every
+case says that it runs on a tape.  Digests are bytes, compared with hashlib's
+for every leaf.
 """
 import concurrent.futures as futures
 import hashlib
@@ -34,22 +36,23 @@ def expected(host, starts, lens, C, alg):
         return b"".join(pool.map(message, range(len(lens))))
 
 
-# (leaves per 256 CUs of the messages of whole chunks, chunk, messages with a
-# tail, the bytes past 16 they start at)
+# (leaves, chunk, messages, all but one of them with a tail, the bytes past 16
+# they start at)
 CASES = [
-    (65536 + 1, 128, 0, 0), (65536 + 100, 384, 3, 0), (70001, 256, 65, 3), (98304, 640, 1000, 0),
-    (131072 + 63, 128, 70, 0), (196608 + 64, 128, 700, 1), (66000, 128, 15000, 0),
+    (65536 + 1, 2048, 1, 0), (65536 + 100, 2176, 4, 0), (70001, 4096, 66, 3), (98304, 2304, 1000, 0),
+    (131072 + 63, 2048, 70, 0), (196608 + 64, 2048, 700, 1), (66000, 4096, 16500, 0), (70000, 4224, 17500, 5),
+    (270000, 4096, 60000, 0),
 ]
 
 
 @pytest.mark.parametrize("alg", ["sha256", "sha384"])
-@pytest.mark.parametrize("n,C,tails,shift", CASES)
-def test_digests(alg, n, C, tails, shift):
+@pytest.mark.parametrize("n,C,count,shift", CASES)
+def test_digests(alg, n, C, count, shift):
+    assert hv.leaf_launch_for(count, n, C, alg) == "tape"
     rng = np.random.default_rng(n + C)
-    whole = np.full(1 + tails // 4, (n - tails) // (1 + tails // 4) * C)
-    whole[0] += (n - tails - whole.sum() // C) * C
-    short = rng.integers(1, C, tails)
-    lens = rng.permutation(np.concatenate((whole, short)))
+    tails = count - 1
+    whole = rng.multinomial(n - tails, np.full(count, 1 / count)) * C
+    lens = rng.permutation(whole + np.concatenate(([0], rng.integers(1, C, tails))))
     starts = shift + np.concatenate(([0], np.cumsum((lens + 15) // 16 * 16)[:-1]))
     buf = W.random_bytes(int(starts[-1] + lens[-1]), 7, DEV)
     table = hv._msg_array(np.uint64(buf.data_ptr()) + starts.astype(np.uint64), lens)
@@ -69,6 +72,7 @@ def test_long_chunks_and_inexact_classes(alg):
     # messages of 8 chunks, so that they are few per leaf
     eight = buf.repeat(8)
     whole = (n - len(tails)) // 8
+    assert hv.leaf_launch_for(whole + len(tails), n, C, alg) == "tape"
     ptrs = np.concatenate((np.full(whole, eight.data_ptr()), np.full(len(tails), buf.data_ptr()))).astype(np.uint64)
     lens = np.concatenate((np.full(whole, 8 * C), tails)).astype(np.uint64)
     got, _ = hv.hv_hash_chunks((ptrs, lens), C, alg=alg)
@@ -100,7 +104,8 @@ def test_a_wave_that_gives_up_hashes_the_chunks_itself(alg):
 
 
 def test_workspace_without_tape_and_repeated_runs():
-    n, C = 70000, 256
+    n, C = 70000, 4096
+    assert hv.leaf_launch_for(1, n, C) == "tape"
     buf = W.random_bytes(n * C - 5, 9, DEV)
     msgs = (np.array([buf.data_ptr()], dtype=np.uint64), np.array([n * C - 5], dtype=np.uint64))
     want, _ = hv.hv_hash_chunks(msgs, C)

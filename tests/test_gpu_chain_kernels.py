@@ -70,6 +70,7 @@ def test_three_groups_per_cu(per_cu, align):
     # workgroup partly filled
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     n = per_cu * cus + (1 if per_cu == 128 else 0)
+    assert hv.leaf_launch_for(n, n, 0) == "three-group"
     rng = np.random.default_rng([per_cu, align])
     lens = rng.integers(0, 12 * 64 - 9, n, endpoint=True)
     lens[rng.integers(0, n, 5)] = 70 * 64 - 9
