@@ -257,12 +257,18 @@ def _msg_array(ptrs: np.ndarray, lens: np.ndarray, host: HostBuffer | None = Non
     return arr
 
 
+# messages from which the library's threads fill a table sooner than numpy's two
+# strided copies (16 host cores: 65,536 messages 0.03 ms by numpy, 0.24 by the
+# library; 600,000 both 0.26; 10^6 0.48 and 0.30)
+_PACK_MIN = 5 << 17
+
+
 def _packed_msgs(ptrs, lens, host: HostBuffer | None = None) -> np.ndarray:
-    """As _msg_array, filled by the library where the arrays can be handed over as they are."""
-    if not all(isinstance(a, np.ndarray) and a.dtype == np.uint64 and a.ndim == 1 and a.flags.c_contiguous
-               and len(a) == len(lens) for a in (ptrs, lens)):
-        return _msg_array(ptrs, lens, host)
+    """As _msg_array, filled by the library where that is faster and the arrays can be handed over as they are."""
     n = len(lens)
+    if n < _PACK_MIN or not all(isinstance(a, np.ndarray) and a.dtype == np.uint64 and a.ndim == 1 and len(a) == n
+                                and a.flags.c_contiguous and a.flags.aligned for a in (ptrs, lens)):
+        return _msg_array(ptrs, lens, host)
     arr = host.get(16 * n).reshape(n, 2) if host is not None else np.empty((n, 2), dtype=np.uint64)
     _check(lib.hv_pack_messages(ptrs.ctypes.data, lens.ctypes.data, n, arr.ctypes.data))
     return arr
