@@ -37,7 +37,7 @@ typedef struct {
     uint64_t chunk_bytes;
     uint64_t n_leaves;
     uint32_t launches[2];  /* Merkle launches of the first tree and of the manifest */
-    uint64_t tiles[2][HV_PLAN_MAX_LAUNCHES];  /* output nodes of each launch */
+    uint64_t tiles[2][HV_PLAN_MAX_LAUNCHES];  /* output nodes of each launch (entries beyond those are the library's) */
 } hv_verify_plan;
 
 /* Device bytes of a plan for these messages; 0 (with hv_last_error set) for

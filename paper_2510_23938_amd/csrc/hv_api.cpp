@@ -313,13 +313,30 @@ hv_status check_segments(const uint64_t* seg_offsets, uint32_t n_seg) {
     return HV_OK;
 }
 
-hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, std::vector<uint64_t>* table, int* launches) {
+hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, bool sha384, std::vector<uint64_t>* table,
+                      int* launches, uint32_t* groups) {
     const size_t row = (size_t)n_seg + 1;
     table->assign(seg_offsets, seg_offsets + row);
-    int k = 0;
+    *groups = 0;
+    int k = 0, short_groups = 0;  // launches so far; group launches of the second kind still to come
     for (;;) {
         const uint64_t entries = (*table)[(size_t)k * row + n_seg];
-        const uint64_t w = merkle_width(entries, n_seg, k + 1);
+        if (short_groups == 0 && merkle_many_short(entries, n_seg, k + 1)) {
+            // an OR instead of the maximum, at a fourth of its time: it is below
+            // the same powers of two, and the rule asks for no others
+            const uint64_t* off = table->data() + (size_t)k * row;
+            uint64_t below = 0;
+            for (uint32_t s = 0; s < n_seg; ++s) {
+                const uint64_t c = off[s + 1] - off[s];
+                below |= c - (c != 0);
+            }
+            short_groups = merkle_short_groups(entries, below + 1, n_seg, k + 1, sha384);
+        }
+        if (short_groups > 0) {
+            *groups |= 1u << k;
+            --short_groups;
+        }
+        const uint64_t w = merkle_grouped(entries, *groups, k + 1) ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
         std::vector<uint64_t> next(row);
         next[0] = 0;
         bool more = false;
@@ -370,12 +387,13 @@ hipError_t stream_cus(hipStream_t stream, uint32_t* cus) {
 hv_status merkle_launch_kinds(hv_alg alg, const uint64_t* seg_offsets, uint32_t n_seg, uint32_t cus, int* launches,
                               int* kind, uint64_t* units, uint64_t* one_lane) {
     std::vector<uint64_t> table;
-    hv_status st = merkle_plan(seg_offsets, n_seg, &table, launches);
+    uint32_t groups = 0;
+    hv_status st = merkle_plan(seg_offsets, n_seg, alg == HV_SHA384, &table, launches, &groups);
     if (st != HV_OK) return st;
     const size_t row = (size_t)n_seg + 1;
     for (int k = 1; k <= *launches; ++k) {
         const uint64_t entries = table[(size_t)(k - 1) * row + n_seg], out = table[(size_t)k * row + n_seg];
-        const bool grouped = merkle_grouped(entries, n_seg, k);
+        const bool grouped = merkle_grouped(entries, groups, k);
         kind[k - 1] = grouped ? 1 : 2;
         units[k - 1] = out;
         one_lane[k - 1] = grouped ? merkle_group_main(out, entries, k == 1, alg == HV_SHA384, cus) : 0;
@@ -384,8 +402,8 @@ hv_status merkle_launch_kinds(hv_alg alg, const uint64_t* seg_offsets, uint32_t 
 }
 
 hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64_t* table, uint32_t n_seg,
-                       uint64_t n_nodes, int launches, const uint64_t* outputs, uint8_t* ping, uint8_t* pong,
-                       hipStream_t stream) {
+                       uint64_t n_nodes, int launches, const uint64_t* outputs, uint32_t groups, uint8_t* ping,
+                       uint8_t* pong, hipStream_t stream) {
     const size_t row = (size_t)n_seg + 1;
     const int a = alg == HV_SHA384 ? hv::kAlgSha384 : hv::kAlgSha256;
     uint32_t cus = 0;
@@ -395,7 +413,7 @@ hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64
         const uint64_t* out_off = table + (size_t)k * row;
         const uint64_t entries = k == 1 ? n_nodes : outputs[k - 2];  // the plan's rule, from the same counts
         hipError_t e;
-        if (merkle_grouped(entries, n_seg, k)) {
+        if (merkle_grouped(entries, groups, k)) {
             if (cus == 0 && (e = stream_cus(stream, &cus)) != hipSuccess) return hip_fail(e, "device query");
             const uint64_t n_main = merkle_group_main(outputs[k - 1], entries, k == 1, alg == HV_SHA384, cus);
             e = hv::launch_merkle_groups(a, in, dst, in_off, out_off, n_seg, outputs[k - 1], n_main, k == 1, stream);
@@ -649,14 +667,15 @@ hv_status hv_merkle_reduce_alg(hv_alg alg, const uint8_t* nodes, const uint64_t*
     const size_t row = (size_t)n_seg + 1;
     std::vector<uint64_t> table;
     int launches = 0;
-    if ((st = merkle_plan(seg_offsets, n_seg, &table, &launches)) != HV_OK) return st;
+    uint32_t groups = 0;
+    if ((st = merkle_plan(seg_offsets, n_seg, alg == HV_SHA384, &table, &launches, &groups)) != HV_OK) return st;
 
     const MerkleLayout L = merkle_layout(workspace, n_nodes, n_seg, D);
     const hipError_t e = hv::upload_table(L.table, table.data(), table.size(), stream);
     if (e != hipSuccess) return hip_fail(e, "plan upload");
     uint64_t outputs[kMaxMerkleLaunches];
     for (int k = 1; k <= launches; ++k) outputs[k - 1] = table[(size_t)k * row + n_seg];
-    return queue_merkle(alg, nodes, roots, L.table, n_seg, n_nodes, launches, outputs, L.ping, L.pong, stream);
+    return queue_merkle(alg, nodes, roots, L.table, n_seg, n_nodes, launches, outputs, groups, L.ping, L.pong, stream);
 }
 
 hv_status hv_merkle_reduce(const uint8_t* nodes, const uint64_t* seg_offsets, uint32_t n_seg, uint8_t* roots,

@@ -116,32 +116,63 @@ hv_status queue_schedule(const hv::MsgDesc* msgs_dev, uint32_t n_msgs, uint64_t 
 // nodes in n_seg segments is a group launch
 //   - from kGroupMinNodes entries on, where the widest levels keep every lane
 //     busy, or
-//   - for more than kManySegments segments of at most 8 entries on average:
+//   - for more than kManySegments segments of at most 8 entries on average,
+//     where one to three group launches save a tile launch (merkle_short_groups):
 //     a tile is a workgroup however few nodes it has, three at a time on a CU,
 //     and reduces them at one wave's latency (20,000 segments of 1 to 13
 //     entries: 886 us), while a group is a lane or four (two launches, see
-//     merkle_group_main: 40 us).  Only the first three launches, so that a few
-//     long segments among the short ones still get tiles.
+//     merkle_group_main: 40 us).
 // Up to 2^31 entries (the per-call limit) that is at most 5 group launches and
-// 2 tile launches, or 3 and 3.
+// 2 tile launches; with launches of the second kind, which start below
+// kGroupMinNodes entries, at most 6 in all.
 constexpr int kMaxMerkleLaunches = 8;
 constexpr uint64_t kGroupMinNodes = (uint64_t)1 << 18;
 constexpr uint32_t kManySegments = 1536;  // two rounds of tiles on 256 CUs
-inline bool merkle_grouped(uint64_t entries, uint32_t n_seg, int k) {
-    return entries >= kGroupMinNodes || (k <= 3 && n_seg > kManySegments && entries <= 8 * (uint64_t)n_seg);
+// Tile launches that reduce a segment of c nodes to one.
+inline int merkle_tile_launches(uint64_t c) {
+    int t = 0;
+    for (; c > 1; ++t) c = (c + hv::kTileNodes - 1) / hv::kTileNodes;
+    return t;
 }
-// Entries one output node of such a launch covers.
-inline uint64_t merkle_width(uint64_t entries, uint32_t n_seg, int k) {
-    return merkle_grouped(entries, n_seg, k) ? (uint64_t)hv::kGroupNodes : (uint64_t)hv::kTileNodes;
+// Whether launch k may be a group launch of the second kind, and is asked next.
+inline bool merkle_many_short(uint64_t entries, uint32_t n_seg, int k) {
+    return k <= 3 && n_seg > kManySegments && entries <= 8 * (uint64_t)n_seg && entries < kGroupMinNodes;
+}
+// The group launches, from launch k on, that save a tile launch of a reduction
+// with `entries` nodes left, at most `longest` in a segment (that, or the next
+// power of two); 0 for a tile launch.  A launch that saves none is time lost
+// (20,000 segments and one of 300,000 entries: 0.97 ms, 1.09 with two more group
+// launches; planning and sending one takes 5 ns a segment, where a tile takes 20
+// even with a single node), unless the tiles have much to hash, four nodes each
+// (40 entries and then 5 each: 1.16 ms, 0.97).  And for up to twice
+// kManySegments only where it saves them all, in two launches at most (one after
+// the first), and not where the tiles are quick, two SHA-384 entries at most: 2,000 segments of up to two
+// entries 98 us with the tile launch, 110 with the group launch; with one of 500
+// among them 101 and 119 (SHA-256), 125 and 168, of 12,000 171 and 192; 5,000
+// 171 and 102, 174 and 131, 171 and 174, 270 and 233.
+inline int merkle_short_groups(uint64_t entries, uint64_t longest, uint32_t n_seg, int k, bool sha384) {
+    const int tiles = merkle_tile_launches(longest) + (k == 1 && longest <= 1 ? 1 : 0);
+    const bool more = n_seg > 2 * kManySegments;
+    if (sha384 && longest <= 2 && !more) return 0;
+    uint64_t c = longest;
+    for (int j = 1; j <= 4 - k; ++j) {
+        c = (c + hv::kGroupNodes - 1) / hv::kGroupNodes;
+        if (more ? merkle_tile_launches(c) < tiles : c <= 1 && j <= (k == 1 ? 2 : 1)) return j;
+    }
+    return more && entries >= 4 * (uint64_t)n_seg ? 1 : 0;
 }
 
 // Host plan of a segmented Merkle reduction over validated segment offsets:
 // `table` gets rows of n_seg + 1 offsets -- row 0 the segment offsets, row k
 // the first output node of each segment after launch k (a segment with c
-// nodes gets max(1, ceil(c / w)) outputs, w = merkle_width(entries of row
-// k - 1, n_seg, k)) -- and `launches` the launch count.  Launch k is a group
-// launch exactly when merkle_grouped(entries of row k - 1, n_seg, k).
-hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, std::vector<uint64_t>* table, int* launches);
+// nodes gets max(1, ceil(c / w)) outputs, w = 8 for a group launch and 512 for
+// a tile launch) -- `launches` the launch count and bit k - 1 of `groups` is set
+// where launch k is a group launch of the second kind above.
+hv_status merkle_plan(const uint64_t* seg_offsets, uint32_t n_seg, bool sha384, std::vector<uint64_t>* table,
+                      int* launches, uint32_t* groups);
+inline bool merkle_grouped(uint64_t entries, uint32_t groups, int k) {
+    return entries >= kGroupMinNodes || ((groups >> (k - 1)) & 1u) != 0;
+}
 
 // Segment offsets: start at 0, never decrease, at most the per-call entry limit.
 hv_status check_segments(const uint64_t* seg_offsets, uint32_t n_seg);
@@ -179,10 +210,10 @@ uint64_t merkle_tiles_bound(uint64_t n_nodes, uint32_t n_seg);
 
 // Queues the launches of a planned reduction: `in` (entries; the first launch
 // forms their leaf hashes) through ping / pong into `out`.  table: the plan's
-// rows on the device; outputs[k]: nodes written by launch k + 1.
+// rows on the device; outputs[k]: nodes written by launch k + 1; groups: the plan's.
 hv_status queue_merkle(hv_alg alg, const uint8_t* in, uint8_t* out, const uint64_t* table, uint32_t n_seg,
-                       uint64_t n_nodes, int launches, const uint64_t* outputs, uint8_t* ping, uint8_t* pong,
-                       hipStream_t stream);
+                       uint64_t n_nodes, int launches, const uint64_t* outputs, uint32_t groups, uint8_t* ping,
+                       uint8_t* pong, hipStream_t stream);
 
 // HIP events around a leaf kernel on `stream` when hv_set_kernel_timing is on
 // for this thread (no-ops otherwise).

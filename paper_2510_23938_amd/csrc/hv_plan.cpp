@@ -50,6 +50,7 @@ struct Prep {
     uint32_t n_seg = 0;
     std::vector<uint64_t> table[2];
     int launches[2] = {0, 0};
+    uint32_t groups[2] = {0, 0};
     size_t rows[2] = {0, 0};
     uint64_t scratch = 0;
 };
@@ -72,15 +73,25 @@ hv_status prepare(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t C, i
         p->n_seg = 1;
         seg = {0, p->n_leaves};
     }
-    if (p->n_seg > 0 && (st = merkle_plan(seg.data(), p->n_seg, &p->table[0], &p->launches[0])) != HV_OK) return st;
+    const bool sha384 = alg == HV_SHA384;
+    if (p->n_seg > 0 && (st = merkle_plan(seg.data(), p->n_seg, sha384, &p->table[0], &p->launches[0], &p->groups[0])) !=
+                            HV_OK)
+        return st;
     if (manifest) {
         const uint64_t top[2] = {0, n_msgs};
-        if ((st = merkle_plan(top, 1, &p->table[1], &p->launches[1])) != HV_OK) return st;
+        if ((st = merkle_plan(top, 1, sha384, &p->table[1], &p->launches[1], &p->groups[1])) != HV_OK) return st;
     }
     p->rows[0] = p->table[0].size();
     p->rows[1] = p->table[1].size();
     p->scratch = scratch_nodes(p->n_leaves, p->n_seg, n_msgs, manifest);
     return HV_OK;
+}
+
+// The plan's group launches of short segments (merkle_plan's `groups`) lie in the
+// last of a tree's tile counts: a reduction with such launches has at most six.
+constexpr int kGroupsAt = HV_PLAN_MAX_LAUNCHES - 1;
+uint32_t plan_groups(const hv_verify_plan* plan, int tree) {
+    return plan->launches[tree] <= (uint32_t)kGroupsAt ? (uint32_t)plan->tiles[tree][kGroupsAt] : 0u;
 }
 
 // Workspace of hv_verify_model: the plan, then its outputs and the comparison buffers.
@@ -157,6 +168,7 @@ hv_status hv_plan_init(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t
         plan->launches[i] = (uint32_t)p.launches[i];
         const uint32_t segs = i == 0 ? p.n_seg : 1;
         for (int k = 0; k < p.launches[i]; ++k) plan->tiles[i][k] = p.table[i][(size_t)(k + 1) * (segs + 1) + segs];
+        if (p.launches[i] <= kGroupsAt) plan->tiles[i][kGroupsAt] = p.groups[i];
     }
     return HV_OK;
 }
@@ -194,12 +206,13 @@ hv_status hv_plan_run(const hv_verify_plan* plan, uint8_t* leaf_digests, uint8_t
     // the first tree has n_leaves entries (per-message segments, or one), the manifest one per message
     if (plan->n_seg > 0 &&
         (st = queue_merkle(plan->alg, leaf_digests, roots, P.table[0], plan->n_seg, plan->n_leaves,
-                           (int)plan->launches[0], plan->tiles[0], P.ping, P.pong, stream)) != HV_OK)
+                           (int)plan->launches[0], plan->tiles[0], plan_groups(plan, 0), P.ping, P.pong, stream)) !=
+            HV_OK)
         return st;
     const uint8_t* top = roots;
     if (plan->manifest) {
         if ((st = queue_merkle(plan->alg, roots, root, P.table[1], 1, plan->n_msgs, (int)plan->launches[1],
-                               plan->tiles[1], P.ping, P.pong, stream)) != HV_OK)
+                               plan->tiles[1], plan_groups(plan, 1), P.ping, P.pong, stream)) != HV_OK)
             return st;
         top = root;
     }

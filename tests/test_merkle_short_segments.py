@@ -13,8 +13,8 @@ def offsets(sizes):
     return np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
 
 
-def kinds(sizes):
-    return [p[0] for p in hv.merkle_launches(offsets(sizes), cus=256)]
+def kinds(sizes, alg="sha256"):
+    return [p[0] for p in hv.merkle_launches(offsets(sizes), alg, cus=256)]
 
 
 def test_launch_plan():
@@ -23,9 +23,22 @@ def test_launch_plan():
     assert kinds([8] * 1537) == ["group"] and kinds([9] * 1537) == ["tile"]  # up to 8 entries on average
     assert kinds([0] * 1537) == ["group"]
     assert kinds([5] * 2000 + [9]) == ["group", "group"]
-    # a long segment among short ones: tiles from the fourth launch on, and no
-    # deeper a chain than without the rule
-    assert kinds([2] * 2000 + [4000]) == ["group", "group", "group", "tile"]
+    # a long segment among short ones: as many group launches as save a tile
+    # launch, tiles where none would be saved
+    assert kinds([2] * 3100 + [4000]) == ["group", "tile"]
+    assert kinds([2] * 3100 + [12000]) == ["group", "group", "tile"]
+    assert kinds([5] * 3073 + [500]) == ["group"] * 3 and kinds([5] * 3071 + [500]) == ["tile"]
+    assert kinds([2] * 2000 + [4000]) == ["tile", "group"] and kinds([2] * 2000 + [12000]) == ["tile", "tile"]
+    assert kinds([5] * 20000 + [300000]) == ["group", "tile", "tile"]
+    assert kinds([8] * 60000 + [12000]) == kinds([9] * 60000 + [12000]) == ["group", "group", "tile"]
+    assert kinds([40] * 60000 + [12000]) == ["group", "group", "tile"]
+    assert kinds([10] * 60000) == ["group", "group"]
+    # or where many nodes each are left to the tiles
+    assert kinds([40] * 20000 + [300000]) == ["group", "group", "tile", "tile"]
+    # nor where the tiles are as quick
+    assert kinds([2] * 3072, "sha384") == ["tile"] and kinds([2] * 3073, "sha384") == ["group"]
+    assert kinds([3] * 1537, "sha384") == ["group"]
+    # no deeper a chain than without the rule
     assert len(kinds([1] * 200000 + [1 << 21])) <= 8
     # four lanes a group up to two rounds of them
     assert hv.merkle_launches(offsets([5] * 20000), cus=256) == [("group", 20000, 0)]
@@ -40,8 +53,9 @@ def test_launch_plan():
 @pytest.mark.parametrize("sizes", [
     [k % 9 for k in range(1537)],                 # every group size, empty ones too, four lanes each
     [k % 14 for k in range(33000)],               # one lane each, two launches
-    [1 + k % 3 for k in range(2000)] + [4000, 0, 513],
-], ids=["four_lanes", "one_lane", "one_long"])
+    [1 + k % 3 for k in range(3100)] + [4000, 0, 513],
+    [1 + k % 3 for k in range(3100)] + [500, 0, 512],
+], ids=["four_lanes", "one_lane", "one_long", "three_launches"])
 def test_roots(alg, sizes):
     D = 32 if alg == "sha256" else 48
     seg = offsets(sizes)
