@@ -28,10 +28,13 @@
  *   - Calls are asynchronous on `stream` unless marked "synchronous".  Input
  *     bytes must stay valid and unmodified until the stream work completes.
  *     Host arrays a call takes (message tables, offset, leaf and dirty lists,
- *     expected roots) are an exception: they are read, and uploaded where the
- *     device needs them, before the call returns, whatever memory they are in
- *     (pageable or pinned); such a call returns once `stream` has reached and
- *     finished its uploads.
+ *     expected roots) are an exception: they are read before the call returns,
+ *     whatever memory they are in (pageable or pinned), and may be changed or
+ *     freed after it.  The return says nothing about `stream`: small tables
+ *     travel in kernel arguments and the call returns at once, larger ones are
+ *     copied and the call returns when the stream has reached the copy.  To
+ *     order other work behind a call, use the stream, an event or a
+ *     synchronisation.
  *   - All argument checks happen before any kernel is queued; on a non-OK
  *     status no kernel was launched (except HV_ERR_HIP, which reports a failed
  *     launch or copy) and hv_last_error() describes the problem.  (A large
@@ -115,8 +118,7 @@ size_t hv_hash_workspace_bytes(uint32_t n_msgs, uint64_t n_leaves);
 /* Chunk digests (Algorithm 1's per-chunk GPU hash): leaf_digests[j] =
  * SHA-256(chunk j) per FIPS 180-4, 32 bytes each in the standard big-endian
  * byte order, leaves numbered as in hv_leaf_layout.
- *   msgs:         host array of n_msgs device messages (read during the call;
- *                 the descriptors are copied to the workspace).
+ *   msgs:         host array of n_msgs device messages (read during the call).
  *   chunk_bytes:  0 or a multiple of 64.
  *   leaf_digests: device, n_leaves * 32 bytes, 16-byte aligned, caller-owned,
  *                 written.
@@ -143,8 +145,8 @@ size_t hv_merkle_workspace_bytes(uint64_t n_nodes, uint32_t n_seg);
  *   seg_offsets: host, n_seg + 1 entries, seg_offsets[0] == 0, non-decreasing.
  *   roots:       device, n_seg * 32 bytes, 16-byte aligned, written.
  *   workspace:   device, >= hv_merkle_workspace_bytes(seg_offsets[n_seg], n_seg).
- * The host plans ceil(depth / 9) launches from seg_offsets and uploads that
- * plan before returning (so the call returns once the stream has reached it).
+ * The host plans at most eight launches from seg_offsets (hv_merkle_launches
+ * in hv_inspect.h lists them) and reads that array before returning.
  * Errors: HV_ERR_INVALID_ARG for n_seg == 0, NULL or misaligned pointers,
  * offsets that do not start at 0 or decrease, more than 2^31 entries;
  * HV_ERR_WORKSPACE; HV_ERR_HIP. */
@@ -203,7 +205,7 @@ hv_status hv_compare_roots_alg(hv_alg alg, const uint8_t* roots, const uint8_t* 
  * the process ends.  That covers, e.g., one message of up to 2,794,794 leaves,
  * or the 723 tensors and 2,153,249 leaves of a 70B-shaped weight set with
  * 64 KiB chunks.  The call makes no hipMalloc, hipFree or other allocation;
- * it runs on the GPU that owns `stream`, and, like hv_hash_chunks, uploads
+ * it runs on the GPU that owns `stream`, and, like hv_hash_chunks, reads
  * the descriptors before it returns.
  * Every call on one GPU shares that GPU's array, and each call rewrites what
  * it reads there: calls whose work may overlap on one GPU (other streams,

@@ -44,8 +44,8 @@ typedef struct {
  * arguments hv_plan_init would reject. */
 size_t hv_plan_bytes(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_bytes, int manifest);
 
-/* Build a plan.  Uploads the host tables before returning (so it returns once the
- * stream has reached them) and queues the scheduling kernels on `stream`.
+/* Build a plan.  Uploads the host tables and queues the scheduling kernels on
+ * `stream`; the host arrays are read before it returns.
  *   msgs: host, n_msgs entries (device addresses), as hv_hash_chunks_alg.
  *   plan_memory: device, >= hv_plan_bytes(...), 256-byte aligned.
  *   plan: host, filled on HV_OK.
@@ -54,7 +54,9 @@ size_t hv_plan_bytes(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t c
 hv_status hv_plan_init(hv_alg alg, const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_bytes, int manifest,
                        void* plan_memory, size_t plan_bytes, hv_verify_plan* plan, hipStream_t stream);
 
-/* One pass of the path, asynchronous on `stream` (kernels only).
+/* One pass of the path, asynchronous on `stream` (kernels only).  The passes of
+ * one plan share the scratch in its memory: passes that may overlap (other
+ * streams, other threads) must be ordered by the caller.
  *   leaf_digests: device, [n_leaves][D] (D = 32 or 48), 16-byte aligned.
  *   roots: device, [n_seg][D], 16-byte aligned (n_seg >= 1 or NULL).
  *   root: device, [1][D], 16-byte aligned: the manifest root (manifest

@@ -231,8 +231,8 @@ class HostBuffer:
     """A growable host byte buffer reused across calls, pinned or pageable.
 
     For the tables a call hands to the library (the message descriptors) and
-    the segment offsets it plans from: the library reads and uploads them
-    before it returns, so the next call may overwrite them.  Reuse saves the
+    the segment offsets it plans from: the library reads them before it
+    returns, so the next call may overwrite them.  Reuse saves the
     page faults of fresh multi-MB arrays, and a pinned descriptor table
     uploads by DMA; with 10^6 messages that shortens the host work ahead of
     each one-shot pass by about a millisecond."""

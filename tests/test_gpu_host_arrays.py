@@ -144,3 +144,61 @@ def test_a_refused_large_table_launches_nothing_and_the_workspace_stays_usable(b
                                hv._stream(DEV))
     torch.cuda.synchronize()
     assert st == hv.HV_OK and np.array_equal(out.cpu().numpy(), want)
+
+
+# offset, leaf and dirty lists, in one launch's arguments, in the most launches'
+# and copied
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("n", [100, 1400, 2800, 5000])
+def test_lists_are_read_during_the_call(n, pinned):
+    def host(values):
+        t = torch.empty(len(values), dtype=torch.int64, pin_memory=pinned)
+        a = t.numpy().view(np.uint64)
+        a[:] = values
+        return a, t
+
+    buf = W.random_bytes(2 * n * 128, 1600, DEV)
+    msgs = (np.array([buf.data_ptr()], dtype=np.uint64), np.array([2 * n * 128], dtype=np.uint64))
+    leaves, _ = hv.hv_hash_chunks(msgs, 128)
+    digests = leaves.cpu().numpy()
+
+    # Merkle segments of one to three entries, then (in bounds) of two
+    sizes = 1 + np.arange(n) % 3
+    sizes[n - n % 3:] = 1
+    seg, keep = host(np.concatenate([[0], np.cumsum(sizes)]))
+    want = [oracle.mth(digests[int(a):int(b)]) for a, b in zip(seg[:-1], seg[1:])]
+    roots = torch.empty((n, 32), dtype=torch.uint8, device=DEV)
+    ws = hv.Workspace(DEV).get(hv.lib.hv_merkle_workspace_bytes(2 * n, n))
+    busy()
+    st = hv.lib.hv_merkle_reduce(leaves.data_ptr(), seg.ctypes.data, n, roots.data_ptr(), ws.data_ptr(), ws.numel(),
+                                 hv._stream(DEV))
+    seg[:] = 2 * np.arange(n + 1)
+    torch.cuda.synchronize()
+    assert st == hv.HV_OK and [bytes(r) for r in roots.cpu().numpy()] == want
+
+    # every other leaf rehashed and updated, then (in bounds) the others
+    offsets, keep2 = host(2 * np.arange(n + 1))
+    stale = leaves.clone()
+    stale[::2] = 0
+    tree = hv.Tree(stale, offsets.copy())
+    listed, keep3 = host(2 * np.arange(n))
+    table = hv._msg_array(*msgs)
+    ws = hv.Workspace(DEV).get(hv.lib.hv_rehash_workspace_bytes(1, n))
+    busy()
+    st = hv.lib.hv_rehash_chunks(table.ctypes.data, 1, 128, listed.ctypes.data, n, stale.data_ptr(), ws.data_ptr(),
+                                 ws.numel(), hv._stream(DEV))
+    table[:] = 0
+    listed[:] = 2 * np.arange(n) + 1
+    torch.cuda.synchronize()
+    assert st == hv.HV_OK and torch.equal(stale, leaves)
+    listed[:] = 2 * np.arange(n)
+    ws = hv.Workspace(DEV).get(hv.lib.hv_tree_update_workspace_bytes(n))
+    busy()
+    st = hv.lib.hv_tree_update(stale.data_ptr(), offsets.ctypes.data, n, tree.buf.data_ptr(), tree.buf.numel(),
+                               listed.ctypes.data, n, tree.roots.data_ptr(), ws.data_ptr(), ws.numel(),
+                               hv._stream(DEV))
+    offsets[:] = 0
+    listed[:] = 2 * np.arange(n) + 1
+    torch.cuda.synchronize()
+    assert st == hv.HV_OK
+    assert [bytes(r) for r in tree.roots.cpu().numpy()] == [oracle.mth(digests[2 * i:2 * i + 2]) for i in range(n)]
