@@ -573,7 +573,7 @@ def main():
     ap.add_argument("--monitor-interval", type=float, default=30.0,
                     help="seconds between sweeps for the averaged cost (the paper's runtime-monitoring example)")
     ap.add_argument("--leaf-kernel", choices=["auto", "one-wave", "two-wave", "two-wave-compact"], default="auto",
-                    help="SHA-256 leaf kernel (auto: the two-wave kernel for at most 128 leaves per CU)")
+                    help="leaf kernel (auto: the kernels named two-wave for at most 128 leaves per CU)")
     ap.add_argument("--graph", action="store_true",
                     help="time HIP-graph replays of the prepared pass (kernel timing from the eager passes)")
     ap.add_argument("--op-rates", action="store_true",

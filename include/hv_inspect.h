@@ -28,13 +28,15 @@ hv_status hv_leaf_schedule(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_b
                            void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 /* Leaf-kernel choice for tests and measurements, per calling thread:
- * 0 = automatic (calls with at most 128 leaves per compute unit of
- * the current device -- 32768 on MI355X -- use the two-wave kernel, which
- * moves the message schedule to other waves (and, with SHA-256, gives a chunk
- * two lanes) and shortens each chunk's chain of blocks; others use the
- * one-wave kernel), 1 = always the one-wave kernel, 2 = always the two-wave
- * kernel, 3 = always the two-wave kernel with twice the chunks, 128, per
- * workgroup (the layout it takes above 64 leaves per compute unit).  From 128 to
+ * 0 = automatic (calls with at most 128 leaves per compute unit of the current
+ * device -- 32768 on MI355X -- use the kernels that shorten each chunk's chain
+ * of blocks, named two-wave here: the message schedule is made by other waves
+ * than the rounds, and a chunk has two lanes, except with SHA-384 above 64
+ * leaves per compute unit; others use the one-wave kernel), 1 = always the
+ * one-wave kernel, 2 = always the two-wave kernel, 3 = always the two-wave
+ * kernel with twice the chunks, 128, per workgroup (the layout it takes above
+ * 64 leaves per compute unit; two lanes per chunk with SHA-256, one with
+ * SHA-384).  From 128 to
  * 192 leaves per compute unit the automatic choice runs SHA-256's three-group
  * kernel (one lane per chunk, the schedules on other waves) in the one-wave
  * kernel's place, and calls and prepared passes for which it pays split the

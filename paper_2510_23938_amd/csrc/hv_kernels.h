@@ -60,7 +60,7 @@ constexpr int kSortBuckets = 4096;   // block-count classes of the tail sort
 
 // Leaf launchers split a call into launches of at most this many leaf-table
 // slots, so a grid stays below a dispatch's 2^32 work-items at two lanes per
-// slot (the two-wave kernels).
+// slot (the chain kernels).
 constexpr uint64_t kMaxSlotsPerLaunch = (uint64_t)1 << 30;
 
 // Scheduler (sched.hip).
@@ -130,14 +130,15 @@ hipError_t launch_sched_range(const MsgDesc* msgs, const Pair* off, uint32_t n, 
 // result[1] = min(result[1], lowest mismatching leaf number).  D is 32 or 48.
 hipError_t launch_monitor_compare(const uint8_t* digests, const uint8_t* ref, uint64_t first, uint64_t k, uint32_t D,
                                   uint64_t* result, hipStream_t s);
-// The two-wave SHA-256 leaf kernel (sha256_split.hip; same contract as
+// The SHA-256 chain kernel (sha256_split.hip; same contract as
 // launch_sha256_leaves), with one or two groups of 64 chunks per workgroup.
 // The automatic choice takes it for up to 128 leaves per compute unit of the
 // current device (32768 on a 256-CU device).
 hipError_t launch_sha256_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                                bool two_groups, hipStream_t s);
-// The two-wave SHA-384 leaf kernel (sha384_split.hip; same contract as
-// launch_sha384_leaves), one or two pairs per workgroup.
+// The SHA-384 chain kernel and, with two_pairs, the kernel of two
+// producer/consumer pairs (sha384_split.hip; same contract as
+// launch_sha384_leaves).
 hipError_t launch_sha384_split(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                                bool two_pairs, hipStream_t s);
 // SHA-384 leaf digests with the kernel the choice selects (the callers' entry),
@@ -147,8 +148,8 @@ hipError_t launch_sha384_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t o
 // What a leaf launch runs (hv_leaf_launch_for's values).
 enum : int {
     kLeafOneWave = 1,
-    kLeafTwoWave = 2,         // 64 chunks per workgroup
-    kLeafTwoWaveCompact = 3,  // 128
+    kLeafTwoWave = 2,         // the chain kernels, 64 chunks per workgroup
+    kLeafTwoWaveCompact = 3,  // 128 chunks: SHA-256's chain kernel, SHA-384's two pairs
     kLeafThreeGroup = 4,      // SHA-256 only
     kLeafTape = 5,            // one-wave over a tape (Tape)
 };
@@ -159,8 +160,8 @@ int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus);
 // query fails, which makes the automatic choices take the one-wave kernels).
 uint32_t device_cus();
 // Leaf-kernel choice of the calling thread (hv_set_leaf_kernel): 0 automatic,
-// 1 one-wave kernel, 2 two-wave kernel, 3 two-wave kernel with 128 chunks per
-// workgroup.
+// 1 one-wave kernel, 2 the kernels for small leaf counts (launch_sha256_split,
+// launch_sha384_split), 3 those with 128 chunks per workgroup.
 int leaf_kernel_choice();
 // SHA-256 leaf digests with the kernel that choice selects (the callers' entry).
 // background: work that shares the chip with other work (monitor scans);

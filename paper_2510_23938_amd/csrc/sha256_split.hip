@@ -613,7 +613,7 @@ uint32_t device_cus() {
 
 int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus) {
     const int choice = leaf_kernel_choice();
-    // the two-wave kernels while every CU holds one workgroup at most: 64
+    // the chain kernels while every CU holds one workgroup at most: 64
     // KiB chunks take 1.18 ms up to 64 per CU and 1.60 up to 128, against 2.69
     // with the one-wave kernel; with more, two workgroups share a CU and the
     // one-wave kernel (or SHA-256's three-group one) is

@@ -1,6 +1,6 @@
-// split_common.h -- pieces shared by the two-wave leaf kernels
-// (sha256_split.hip, sha384_split.hip): global-memory pointer types and a
-// barrier that orders LDS only.
+// split_common.h -- pieces shared by the leaf kernels that make the message
+// schedule on other waves than the rounds (sha256_split.hip, sha384_split.hip):
+// global-memory pointer types and a barrier that orders LDS only.
 #pragma once
 #include <stdint.h>
 #include <hip/hip_runtime.h>

@@ -601,14 +601,16 @@ def measure_hbm_read(nbytes=16 << 30, device="cuda", grid=None, reps=5) -> dict:
 
 
 def set_leaf_kernel(choice: str):
-    """Leaf kernel (SHA-256 and SHA-384) for this thread: "auto", "one-wave", "two-wave" or
-    "two-wave-compact" (two producer/consumer pairs per workgroup); digests do not depend on it."""
+    """Leaf kernel (SHA-256 and SHA-384) for this thread: "auto", "one-wave", "two-wave" (the kernels for
+    small leaf counts, the message schedule made by other waves than the rounds) or "two-wave-compact"
+    (those with 128 chunks per workgroup in place of 64); digests do not depend on it."""
     _check(lib.hv_set_leaf_kernel({"auto": 0, "one-wave": 1, "two-wave": 2, "two-wave-compact": 3}[choice]))
 
 
 def leaf_kernel_for(n_leaves: int) -> str:
     """The leaf kernel a hash call over n_leaves leaves runs on the current device under this thread's
-    choice: "one-wave", "two-wave" or "two-wave-compact" (two producer/consumer pairs per workgroup)."""
+    choice: "one-wave" (also where it takes the three-group kernel or a tape, see leaf_launch_for), "two-wave"
+    or "two-wave-compact"."""
     k = ctypes.c_int(0)
     _check(lib.hv_leaf_kernel_for(int(n_leaves), ctypes.byref(k)))
     return {1: "one-wave", 2: "two-wave", 3: "two-wave-compact"}[k.value]
