@@ -83,8 +83,10 @@ struct TapeWalk {
         // at the interval's start the group's first blocks; at its end the last ones
         p->last = left == 0;
         const uint32_t from = p->last ? (uint32_t)(len - here) : 0u, to = from + (uint32_t)here;
-        p->from = from > setup ? from - setup : 0u;
-        p->to = to > setup ? to - setup : 0u;
+        // a cut lies on an even block: two SHA-256 blocks are a stage and a
+        // 128-byte line, and from an odd one on every stage would be of two lines
+        p->from = from > setup ? (from - setup) & ~1u : 0u;
+        p->to = p->last ? to - setup : to > setup ? (to - setup) & ~1u : 0u;
         pos += here;
         start += len;
         ++group;

@@ -149,7 +149,7 @@ def test_a_refused_large_table_launches_nothing_and_the_workspace_stays_usable(b
 # offset, leaf and dirty lists, in one launch's arguments, in the most launches'
 # and copied
 @pytest.mark.parametrize("pinned", [False, True])
-@pytest.mark.parametrize("n", [100, 1400, 2800, 5000])
+@pytest.mark.parametrize("n", [100, 1900, 3800, 5000])
 def test_lists_are_read_during_the_call(n, pinned):
     def host(values):
         t = torch.empty(len(values), dtype=torch.int64, pin_memory=pinned)

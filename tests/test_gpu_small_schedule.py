@@ -55,8 +55,8 @@ def test_rehash(n, C):
 
 
 # Tables that fill a launch's arguments (480 words, 960 where they fit 32 bits)
-# or all three launches', and one message or leaf more.
-@pytest.mark.parametrize("n,k", [(240, 960), (241, 961), (720, 2880), (721, 2881), (1440, 5760), (1441, 5761)])
+# or all four launches', and one message or leaf more.
+@pytest.mark.parametrize("n,k", [(240, 960), (241, 961), (960, 3840), (961, 3841), (1440, 5760), (1441, 5761)])
 def test_tables_in_arguments(n, k):
     lens = np.full(n, 128 * 6, dtype=np.uint64)
     buf = torch.zeros(int(lens.sum()), dtype=torch.uint8, device="cuda").random_(0, 256)

@@ -47,7 +47,7 @@ int main() {
                 CHECK(p.group < full + tails);
                 if (!p.last) {
                     CHECK(n == 0);  // at its interval's start: the states are there first
-                    CHECK(p.from == 0 && p.to < len[p.group]);
+                    CHECK(p.from == 0 && p.to < len[p.group] && p.to % 2 == 0);
                     upto[p.group] = p.to;
                     by[p.group] = w + 1;
                 } else {
@@ -57,7 +57,7 @@ int main() {
                 }
                 length += p.to - p.from;
             }
-            CHECK(length <= (at + waves - 1) / waves || length <= longest);
+            CHECK(length <= (at + waves - 1) / waves + 1 || length <= longest);  // a cut lies on an even block
         }
         for (uint64_t g = 0; g < full + tails; ++g) CHECK(done[g] == 1);
     }
