@@ -68,13 +68,14 @@ hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t s);
 // Copies a host table of n words to the device; `from` is read before the call
 // returns.  A pageable copy waits for the stream and is waited for, so the
 // kernels behind it start some 20 us after the ones before it end; tables of up
-// to 11 KB (23 KB where every word fits 32 bits) go as launch arguments
-// instead, at most three launches of about 4 us: a one-shot call over 24 short
-// tensors 163 -> 138 us, over 720 222 -> 204, an update of 1000 chunks 1.60 ->
-// 1.56 ms.  With more launches the copy is as fast or faster: leaf digests of
-// 1,025 messages 115 us with five launches and 107 with the copy, an update of
-// 5,760 chunks 219 and 188.  A stream under capture gets the copy whatever the
-// size.
+// to 15 KB (30 KB where every word fits 32 bits) go as launch arguments
+// instead, at most four launches of about 4 us: a one-shot call over 24 short
+// tensors 163 -> 138 us, over 720 222 -> 204; rehashing 1000 chunks and updating
+// the tree above them, its table behind the leaf kernel in the stream, 1.47 ->
+// 1.43 ms.  Four launches on an idle stream take as long as the copy, and with
+// more the copy is faster: leaf digests of 1,025 messages 115 us with five
+// launches and 107 with the copy, a tree update of 5,760 leaves 219 and 188.  A
+// stream under capture gets the copy whatever the size.
 hipError_t upload_table(uint64_t* to, const uint64_t* from, size_t n, hipStream_t s);
 hipError_t launch_sched_count(const MsgDesc* msgs, uint32_t n, uint64_t C, Pair* cnt, hipStream_t s);
 size_t scan_partials_count(size_t n);

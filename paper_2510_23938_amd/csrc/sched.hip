@@ -501,7 +501,7 @@ hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t s) {
 }
 
 hipError_t upload_table(uint64_t* to, const uint64_t* from, size_t n, hipStream_t s) {
-    constexpr size_t kLaunches = 3;
+    constexpr size_t kLaunches = 4;
     if (n <= kLaunches * kArgBytes / sizeof(uint32_t)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         const hipError_t e = hipStreamIsCapturing(s, &capture);
