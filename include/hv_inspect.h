@@ -39,7 +39,7 @@ hv_status hv_leaf_schedule(const hv_msg* msgs, uint32_t n_msgs, uint64_t chunk_b
  * SHA-384).  From 128 to
  * 192 leaves per compute unit the automatic choice runs SHA-256's three-group
  * kernel (one lane per chunk, the schedules on other waves) in the one-wave
- * kernel's place, and calls and prepared passes for which it pays split the
+ * kernel's place unless the chunk size is 512 bytes or less, and calls and prepared passes for which it pays split the
  * one-wave kernel's work evenly over the resident waves, chunks cut between
  * them (hv_leaf_launch_for says which; a forced choice runs the kernel it
  * names).  Monitor scans (hv_monitor.h) take the

@@ -54,6 +54,11 @@ HashLayout hash_layout(void* ws, uint32_t n_msgs, uint64_t n_leaves) {
 
 int leaf_launch(hv_alg alg, uint32_t n_msgs, uint64_t chunk_bytes, uint64_t n_leaves, uint32_t cus, uint32_t* waves) {
     const int k = hv::leaf_launch_for(alg == HV_SHA384 ? hv::kAlgSha384 : hv::kAlgSha256, n_leaves, false, cus);
+    // chunks of a few blocks are over before three groups' schedules run ahead:
+    // 40,000 of 256 bytes 22.6 us and 21.2 with the one-wave kernel, unaligned
+    // 25.7 and 21.4; of 512 bytes 31.4 and 32.2, unaligned 35.3 and 32.6; of 2 KiB
+    // unaligned 95 and 97
+    if (k == hv::kLeafThreeGroup && chunk_bytes != 0 && chunk_bytes <= 512) return hv::kLeafOneWave;
     if (k != hv::kLeafOneWave || hv::leaf_kernel_choice() != 0 || !tape_worth(n_msgs, n_leaves) ||
         !tape_chunks(n_msgs, n_leaves, chunk_bytes))
         return k;
@@ -69,7 +74,8 @@ hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_
                          uint64_t n_leaves, uint8_t* digests, hipStream_t stream) {
     const bool sha384 = alg == HV_SHA384;
     hv::Tape t = L.tape;
-    if (tape && leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves) == hv::kLeafTape) {
+    const int k = leaf_launch(alg, n_msgs, chunk_bytes, n_leaves, hv::device_cus(), &t.waves);
+    if (k == hv::kLeafTape && tape) {
         t.setup = sha384 ? hv::kTapeSetup384 : hv::kTapeSetup256;
         t.full_len = (sha384 ? chunk_bytes / 128 + 1 : chunk_bytes / 64 + 1) + t.setup;
         t.polls = g_tape_polls == 0 || t.full_len < g_tape_polls ? g_tape_polls : (uint32_t)t.full_len;
@@ -79,6 +85,9 @@ hipError_t launch_leaves(hv_alg alg, const HashLayout& L, bool tape, uint32_t n_
         return sha384 ? hv::launch_sha384_tape(L.desc, n_leaves, n_leaves, digests, t, stream)
                       : hv::launch_sha256_tape(L.desc, n_leaves, n_leaves, digests, t, stream);
     }
+    if (k == hv::kLeafTape || k == hv::kLeafOneWave)
+        return sha384 ? hv::launch_sha384_leaves(L.desc, n_leaves, n_leaves, digests, stream)
+                      : hv::launch_sha256_leaves(L.desc, n_leaves, n_leaves, digests, stream);
     return sha384 ? hv::launch_sha384_auto(L.desc, n_leaves, n_leaves, digests, stream)
                   : hv::launch_sha256_auto(L.desc, n_leaves, n_leaves, digests, stream);
 }

@@ -34,6 +34,12 @@ def test_rule_by_leaf_count():
         assert launch(256 * CU + 1, alg, msgs=20000) == "one-wave"  # many tails
 
 
+def test_short_chunks_of_three_groups_per_cu():
+    n = 150 * CU
+    assert [launch(n, C=C) for C in (128, 256, 512)] == ["one-wave"] * 3
+    assert [launch(n, C=C) for C in (576, 1024, 0)] == ["three-group"] * 3
+
+
 def test_short_chunks_and_many_leaves_keep_the_plain_launch():
     # the tape lost there: three waves on a SIMD, and a launch for its plan
     for alg in ("sha256", "sha384"):
