@@ -44,7 +44,7 @@ struct Tape {
 // 4 KiB, a fourth of them tails of 100 bytes, 279 us against 184 with the plain
 // launch, 188 with them; SHA-384, the tails of every length, 288 and 207, 216.
 // Where nearly all chunks are whole ones they change nothing (205,697 of 64 KiB:
-// 7.81 ms without, 7.83 with them).
+// 7.81 ms without, 7.80 with them).
 constexpr uint32_t kTapeSetup256 = 3, kTapeSetup384 = 2;
 // Looks of a wave that waits for another's states, at least; for chunks of more
 // blocks than that, one for each block, which is still less than the time they
@@ -167,7 +167,7 @@ int leaf_kernel_choice();
 // SHA-256 leaf digests with the kernel that choice selects (the callers' entry).
 // background: work that shares the chip with other work (monitor scans);
 // under the automatic choice it takes the one-wave kernel, which hashes a byte
-// in the least CU time, rather than the one with the shortest chains.
+// with the fewest instructions, rather than the one with the shortest chains.
 hipError_t launch_sha256_auto(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,
                               hipStream_t s, bool background = false);
 hipError_t launch_sha256_leaves(const LeafDesc* desc, uint64_t n_slots, uint64_t out_bound, uint8_t* digests,

@@ -617,8 +617,10 @@ int leaf_launch_for(int alg, uint64_t n_slots, bool background, uint64_t cus) {
     // KiB chunks take 1.18 ms up to 64 per CU and 1.60 up to 128, against 2.69
     // with the one-wave kernel; with more, two workgroups share a CU and the
     // one-wave kernel (or SHA-256's three-group one) is
-    // faster.  Background work keeps the one-wave kernel:
-    // shorter chains cost more instructions, about 1.4x the CU time per byte.
+    // faster.  Background work keeps the one-wave kernel: beside decode-shaped
+    // products a chain kernel scans 2.2 times as fast and costs them 1.8 times
+    // as much at slices of 4,096 chunks (15.4% against 8.5%), 7 times at 16,384
+    // (80% against 11%).
     if (choice == 1 || (choice == 0 && (background || n_slots > 128 * cus))) {
         // SHA-256, up to three groups per CU, one workgroup each: 2.07 ms
         // against 2.72 for 64 KiB chunks (above kSent); with more, the one-wave
