@@ -334,9 +334,46 @@ static void merkle_plans(void) {
     CHECK(st == HV_OK || st == HV_ERR_HIP);
 }
 
+/* Plans of many short segments with a few long ones among them, where group
+ * launches below 2^18 entries save tile launches: every launch's outputs are
+ * what its kind makes of the level before, the chain ends with one node per
+ * segment, and the workspace holds the plan's rows and its widest levels. */
+static void short_segment_plans(void) {
+    enum { MAXSEG = 20000 };
+    static uint64_t seg[MAXSEG + 1], len[MAXSEG];
+    int groups_below = 0;
+    for (int it = 0; it < 1500; ++it) {
+        const uint32_t n_seg = 1400 + (uint32_t)(next() % (it % 10 == 0 ? MAXSEG - 1400 : 3200));
+        const uint64_t most = next() % 12;
+        seg[0] = 0;
+        for (uint32_t i = 0; i < n_seg; ++i) len[i] = next() % (most + 1);
+        for (uint64_t k = next() % 3; k > 0; --k) len[next() % n_seg] = next() % ((uint64_t)1 << (next() % 20));
+        for (uint32_t i = 0; i < n_seg; ++i) seg[i + 1] = seg[i] + len[i];
+        const hv_alg alg = (next() & 1) ? HV_SHA384 : HV_SHA256;
+        int launches = 0, kind[8];
+        uint64_t units[8], one[8], widest = 0, entries = seg[n_seg];
+        CHECK(hv_merkle_launches(alg, seg, n_seg, 256, &launches, kind, units, one) == HV_OK);
+        CHECK(launches >= 1 && launches <= 7);
+        for (int k = 0; k < launches; ++k) {
+            const uint64_t w = kind[k] == 1 ? 8 : 512;
+            if (kind[k] == 1 && entries < ((uint64_t)1 << 18)) ++groups_below;
+            uint64_t out = 0;
+            for (uint32_t i = 0; i < n_seg; ++i) out += len[i] = len[i] <= w ? 1 : (len[i] + w - 1) / w;
+            CHECK(units[k] == out && one[k] <= out);
+            if (k + 1 < launches && out > widest) widest = out;
+            entries = out;
+        }
+        CHECK(entries == n_seg);
+        const uint64_t rows = ((uint64_t)launches + 1) * (n_seg + 1) * 8, level = widest * (alg == HV_SHA384 ? 48 : 32);
+        CHECK(hv_merkle_workspace_bytes_alg(alg, seg[n_seg], n_seg) >= rows + 2 * level);
+    }
+    CHECK(groups_below > 300);
+}
+
 int main(void) {
     layouts_and_sizes();
     merkle_plans();
+    short_segment_plans();
     large_layouts();
     stream_plans();
     tree_sizes();
