@@ -324,22 +324,23 @@ __device__ __forceinline__ uint64_t own_part(uint64_t x3, const Half& c, uint64_
 // the hardware does not wait for and the compiler, which does not see into the
 // blocks, does not add waits for: VCC may be read by a vector instruction no
 // sooner than two instructions after one wrote it, so the halves have at least
-// two instructions between them, and a DPP operand no sooner than two after it
-// is written (`fresh` waits that out, elsewhere y is a step old).
+// two instructions between them (the blocks are volatile, which keeps their
+// order with others), and a DPP operand no sooner than two after it is written
+// (`fresh` waits that out, elsewhere y is a step old).
 // tests/test_isa_waits.py reads both distances in the kernel's code.
 __device__ __forceinline__ uint32_t add_partner_low(uint32_t x, uint32_t y, uint64_t& carry) {
     uint32_t r;
     register uint64_t vcc asm("vcc");
-    asm("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-        : "=v"(r), "=s"(vcc) : "v"(y), "v"(x));
+    asm volatile("v_add_co_u32_dpp %0, vcc, %2, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+                 : "=v"(r), "=s"(vcc) : "v"(y), "v"(x));
     carry = vcc;
     return r;
 }
 __device__ __forceinline__ uint32_t add_partner_high(uint32_t x, uint32_t y, uint64_t carry) {
     uint32_t r;
     register uint64_t vcc asm("vcc") = carry;  // written too
-    asm("v_addc_co_u32_dpp %0, vcc, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-        : "=v"(r), "+s"(vcc) : "v"(y), "v"(x));
+    asm volatile("v_addc_co_u32_dpp %0, vcc, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+                 : "=v"(r), "+s"(vcc) : "v"(y), "v"(x));
     return r;
 }
 // Both at once, with the waits.
@@ -375,23 +376,21 @@ __device__ __forceinline__ void step(uint64_t R[4], const Half& c, uint64_t& q, 
     HV_PIN;
     const uint64_t y = bitop3_64<0x96>(x0, i, j);
     HV_PIN;
-    // where a branch follows, the compiler may move what is between the halves
-    // behind it
-    constexpr bool split = s != 63 && s < 80;
     uint64_t carry = 0;
     uint32_t low = 0;
-    if constexpr (split) low = add_partner_low(lo32(own), lo32(x0), carry);
+    if constexpr (s < 81) low = add_partner_low(lo32(own), lo32(x0), carry);
     HV_PIN;
-    const uint64_t f = bitop3_64<0xCA>(p, x2, x1);  // Maj(a, b, c), or Ch(e, f, g)
+    uint64_t f = bitop3_64<0xCA>(p, x2, x1);  // Maj(a, b, c), or Ch(e, f, g)
+    // where a branch follows the step, the compiler would move this behind it,
+    // and the halves would be neighbours.  (With waits there instead, which are 4
+    // bytes each and shift what follows: 26 chunks of 128 KiB 2.94 ms, so 2.92.)
+    if constexpr (s == 63 || s == 80) asm volatile("" : "+v"(f));
     HV_PIN;
     const uint64_t sigma = rotr64_below_32(y, c.r3);
     HV_PIN;
     const uint64_t t = f + q;
     HV_PIN;
-    if constexpr (split)
-        q = pack(add_partner_high(hi32(own), hi32(x0), carry), low);
-    else
-        q = add_partner_fresh(own, x0);
+    if constexpr (s < 81) q = pack(add_partner_high(hi32(own), hi32(x0), carry), low);
     HV_PIN;
     R[(3 - s) & 3] = sigma + t;
     HV_PIN;
